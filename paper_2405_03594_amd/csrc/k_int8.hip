@@ -39,6 +39,10 @@ constexpr int kI8OffsetLanes = kWave - 1;
 // Batches from this size on use the prefill kernels' MFMA tiling (activations staged in LDS and
 // shared by the row blocks of a workgroup) instead of the streaming kernels below.
 constexpr int64_t kI8PrefillMinM = 128;
+// Batches of more rows than one batch fragment go to the streaming kernel that stages activations through
+// LDS, where it can address them: per launch, this file's kernel / that one, q|k|v 13.9 / 14.4 us at 16
+// rows, 20.4 / 18.7 at 32, 55.1 / 32.2 at 127; gate|up 21.1 / 28.3, 34.6 / 30.9, 95.6 / 61.0.
+constexpr int64_t kI8WideMinM = 17;
 
 __device__ __forceinline__ i32x4 mfma_i8(u32x4 a, u32x4 b, i32x4 c) {
   return __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x4, b), c, 0, 0,
@@ -505,6 +509,9 @@ hipError_t launch_sparse_int8(const spl_int8_task* tasks, int count, int64_t M, 
     }
     return hipSuccess;
   }
+  bool wide = M >= kI8WideMinM;
+  for (int i = 0; i < count; ++i) wide = wide && sparse_wide_fits(M, tasks[i].Wq->cols, 1);
+  if (wide) return launch_int8_wide(tasks, count, M, s);
   I8GroupArg g{};
   g.count = count;
   g.M = (int32_t)M;

@@ -14,6 +14,11 @@ constexpr int64_t kMaxDim = (int64_t)1 << 31;        // N, K, M < 2^31
 constexpr int64_t kMaxElems = (int64_t)1 << 40;      // N * K, M * K, M * N
 constexpr int64_t kDecodeMaxM = 32;
 constexpr int64_t kGatedDecodeMaxM = 16;           // the paired decode kernel holds one 16-row batch tile
+// AUTO: the decode kernel up to this many rows, then the streaming kernel of
+// several batch fragments as far as it goes (spl::kWideMaxM; the gated half:
+// kGatedWideMaxM), then the prefill kernels.
+constexpr int64_t kStreamMaxM = 1;
+constexpr int64_t kGatedWideMaxM = 112;
 // The decode kernels address the activations [M][K] with 32-bit byte offsets.
 bool decode_fits(int64_t M, int64_t K) { return M <= kDecodeMaxM && 2 * M * K <= ((int64_t)1 << 31); }
 
@@ -240,6 +245,7 @@ spl_status spl_sparse_linear_group(const spl_sparse_task* tasks, int32_t count, 
   if (!tasks || count < 1 || count > SPL_MAX_GROUP || M < 0) return SPL_ERR_INVALID_ARG;
   int64_t blocks = 0;
   int32_t resolved = algo;
+  bool wide = algo == SPL_ALGO_AUTO && M > kStreamMaxM;
   for (int32_t i = 0; i < count; ++i) {
     if (!tasks[i].W) return SPL_ERR_INVALID_ARG;
     int32_t a = algo;
@@ -247,11 +253,13 @@ spl_status spl_sparse_linear_group(const spl_sparse_task* tasks, int32_t count, 
     if (st != SPL_OK) return st;
     if (tasks[i].W->dtype != tasks[0].W->dtype) return SPL_ERR_INVALID_ARG;
     resolved = a;                                      // AUTO depends on M only: the same for every task
+    wide = wide && spl::sparse_wide_fits(M, tasks[i].W->cols, 2);
     blocks += spl::tile_blocks(tasks[i].W->rows);
   }
   if (blocks >= kMaxDim) return SPL_ERR_OVERFLOW;
   if (M == 0) return SPL_OK;
   (void)hipGetLastError();
+  if (wide) return launched(spl::launch_sparse_wide(tasks, count, M, stream));
   if (resolved == SPL_ALGO_DECODE) return launched(spl::launch_sparse_decode(tasks, count, M, stream));
   for (int32_t i = 0; i < count; ++i) {
     const spl_status st = launched(spl::launch_sparse_prefill(tasks[i].X, M, *tasks[i].W, tasks[i].Y, stream));
@@ -279,6 +287,8 @@ spl_status spl_sparse_linear_silu_mul(const void* X, int64_t M, const spl_matrix
   if (2 * spl::tile_blocks(Wgate->rows) >= kMaxDim) return SPL_ERR_OVERFLOW;
   if (M == 0) return SPL_OK;
   (void)hipGetLastError();
+  if (algo == SPL_ALGO_AUTO && M <= kGatedWideMaxM && spl::sparse_wide_fits(M, Wgate->cols, 2))
+    return launched(spl::launch_gated_wide(X, M, *Wgate, *Wup, Y, stream));
   if (ag == SPL_ALGO_DECODE) return launched(spl::launch_gated_decode(X, M, *Wgate, *Wup, Y, stream));
   return launched(spl::launch_gated_prefill(X, M, *Wgate, *Wup, Y, stream));
 }
@@ -555,6 +565,7 @@ spl_status spl_dense_linear_group(const spl_dense_task* tasks, int32_t count, in
   if (!tasks || count < 1 || count > SPL_MAX_GROUP || M < 0) return SPL_ERR_INVALID_ARG;
   int64_t blocks = 0;
   int32_t resolved = algo;
+  bool wide = algo == SPL_ALGO_AUTO && M > kStreamMaxM;
   for (int32_t i = 0; i < count; ++i) {
     int32_t a = algo;
     const spl_status st = check_dense_task(&tasks[i], M, dtype, &a);

@@ -203,6 +203,15 @@ hipError_t launch_zero_fill(void* Y, int64_t count16, hipStream_t s);
 // Decode kernels over a group of 1..SPL_MAX_GROUP validated tasks (one launch).
 hipError_t launch_sparse_decode(const spl_sparse_task* tasks, int count, int64_t M, hipStream_t s);
 hipError_t launch_dense_decode(const spl_dense_task* tasks, int count, int64_t M, int32_t dtype, hipStream_t s);
+// Streaming kernel for batches of up to kWideMaxM rows whose activations
+// (`bytes` each) it can address: groups of 1..SPL_MAX_GROUP validated tasks,
+// the gated half of an MLP, int8 groups.
+constexpr int64_t kWideMaxM = 128;
+bool sparse_wide_fits(int64_t M, int64_t K, int bytes);
+hipError_t launch_sparse_wide(const spl_sparse_task* tasks, int count, int64_t M, hipStream_t s);
+hipError_t launch_gated_wide(const void* X, int64_t M, const spl_matrix& Wg, const spl_matrix& Wu, void* Y,
+                             hipStream_t s);
+hipError_t launch_int8_wide(const spl_int8_task* tasks, int count, int64_t M, hipStream_t s);
 hipError_t launch_sparse_prefill(const void* X, int64_t M, const spl_matrix& Wc, void* Y, hipStream_t s);
 hipError_t launch_dense_prefill(const void* X, int64_t M, const void* W, int32_t dtype, int64_t N, int64_t K,
                                 void* Y, hipStream_t s);
