@@ -90,8 +90,8 @@ typedef enum { SPL_F16 = 1, SPL_BF16 = 2, SPL_I8 = 3, SPL_I4 = 4 } spl_dtype;
  * to four batch fragments per expanded tile for 2 <= M <= 128 (the gated half:
  * M <= 112, and from one row on), then PREFILL.  DECODE is the small-batch
  * kernel (M <= 32): compressed rows are decompressed into MFMA operand tiles
- * with the batch padded to 16 or 32.  PREFILL is the large-batch tiled kernel: compressed
- * tiles are decompressed into LDS and feed bf16/fp16 MFMA (any M). */
+ * with the batch padded to 16 or 32.  PREFILL is the large-batch tiled kernel:
+ * compressed tiles are decompressed into LDS and feed bf16/fp16 MFMA (any M). */
 typedef enum { SPL_ALGO_AUTO = 0, SPL_ALGO_DECODE = 1, SPL_ALGO_PREFILL = 2 } spl_algo;
 
 typedef enum { SPL_LAYOUT_ROWS = 0, SPL_LAYOUT_TILE16 = 1 } spl_layout;
@@ -457,6 +457,35 @@ spl_status spl_sparse_linear_group(const spl_sparse_task* tasks, int32_t count, 
 spl_status spl_dense_linear_group(const spl_dense_task* tasks, int32_t count, int64_t M, int32_t dtype,
                                   int32_t algo, hipStream_t stream);
 
+/* The same calls with scratch memory lent by the caller (AUTO).  With it, large
+ * batches are multiplied through a decoded copy of the weights in matrix-core
+ * operand order (paper section 2.4.2 decompresses the stored submatrices
+ * before the matrix units consume them): each tile is decoded once per call
+ * instead of once per block of batch rows, and the products of a group run as
+ * one launch.  The results are those of the plain call up to the order of the
+ * fp32 sums (int8: identical).
+ *   *_scratch_bytes  device bytes the call can use; 0 where it would use none
+ *                    (small batches, or sizes past the decoded product's
+ *                    32-bit addressing); -1 for arguments the call rejects.
+ *   scratch          256-byte aligned, caller-owned, overwritten; NULL, or
+ *                    scratch_bytes below what the size function returns, gives
+ *                    the plain call.  One buffer can serve calls in turn on
+ *                    one stream.
+ * spl_sparse_input_grad_scratch computes spl_sparse_input_grad through W's
+ * decoded transpose (rows % 8 == 0); its size function returns 0 otherwise and
+ * the call is then SPL_ERR_UNSUPPORTED without scratch (it has no other
+ * workspace). */
+int64_t spl_sparse_linear_group_scratch_bytes(const spl_sparse_task* tasks, int32_t count, int64_t M);
+spl_status spl_sparse_linear_group_scratch(const spl_sparse_task* tasks, int32_t count, int64_t M, void* scratch,
+                                           int64_t scratch_bytes, hipStream_t stream);
+int64_t spl_sparse_linear_silu_mul_scratch_bytes(int64_t M, const spl_matrix* Wgate, const spl_matrix* Wup);
+spl_status spl_sparse_linear_silu_mul_scratch(const void* X, int64_t M, const spl_matrix* Wgate,
+                                              const spl_matrix* Wup, void* Y, void* scratch, int64_t scratch_bytes,
+                                              hipStream_t stream);
+int64_t spl_sparse_input_grad_scratch_bytes(int64_t M, const spl_matrix* Wc);
+spl_status spl_sparse_input_grad_scratch(const void* dY, int64_t M, const spl_matrix* Wc, void* dX, void* scratch,
+                                         int64_t scratch_bytes, hipStream_t stream);
+
 /* Grouped sparse-quantized launches (paper section 3.4): up to SPL_MAX_GROUP
  * independent int8 linear layers that share the batch size M, one kernel
  * launch for all of them.  Each task carries the arguments of
@@ -487,6 +516,10 @@ typedef struct {
 } spl_dense_int8_task;
 
 spl_status spl_sparse_linear_int8_group(const spl_int8_task* tasks, int32_t count, int64_t M, hipStream_t stream);
+/* With scratch, as spl_sparse_linear_group_scratch. */
+int64_t spl_sparse_linear_int8_group_scratch_bytes(const spl_int8_task* tasks, int32_t count, int64_t M);
+spl_status spl_sparse_linear_int8_group_scratch(const spl_int8_task* tasks, int32_t count, int64_t M, void* scratch,
+                                                int64_t scratch_bytes, hipStream_t stream);
 spl_status spl_dense_linear_int8_group(const spl_dense_int8_task* tasks, int32_t count, int64_t M,
                                        hipStream_t stream);
 

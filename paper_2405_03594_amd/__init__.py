@@ -113,6 +113,14 @@ def lib() -> ctypes.CDLL:
         "spl_sparse_linear_ex": (ctypes.c_int, [P, I64, MP, P, I32, P]),
         "spl_sparse_linear_expanded_workspace_bytes": (I64, [MP]),
         "spl_sparse_linear_expanded": (ctypes.c_int, [P, I64, MP, P, P, P]),
+        "spl_sparse_linear_group_scratch_bytes": (I64, [ctypes.POINTER(_SparseTask), I32, I64]),
+        "spl_sparse_linear_group_scratch": (ctypes.c_int, [ctypes.POINTER(_SparseTask), I32, I64, P, I64, P]),
+        "spl_sparse_linear_silu_mul_scratch_bytes": (I64, [I64, MP, MP]),
+        "spl_sparse_linear_silu_mul_scratch": (ctypes.c_int, [P, I64, MP, MP, P, P, I64, P]),
+        "spl_sparse_linear_int8_group_scratch_bytes": (I64, [ctypes.POINTER(_Int8Task), I32, I64]),
+        "spl_sparse_linear_int8_group_scratch": (ctypes.c_int, [ctypes.POINTER(_Int8Task), I32, I64, P, I64, P]),
+        "spl_sparse_input_grad_scratch_bytes": (I64, [I64, MP]),
+        "spl_sparse_input_grad_scratch": (ctypes.c_int, [P, I64, MP, P, P, I64, P]),
         "spl_sparse_linear_int8": (ctypes.c_int, [P, P, I64, MP, P, P, P, P]),
         "spl_sparse_linear_int8_expanded": (ctypes.c_int, [P, P, I64, MP, P, P, P, P, P]),
         "spl_quantize_rows_i8": (ctypes.c_int, [P, ctypes.c_int32, I64, I64, P, P, P]),
@@ -162,6 +170,26 @@ def _ptr(t: torch.Tensor | None):
 def _stream(stream) -> ctypes.c_void_p:
     s = stream if stream is not None else torch.cuda.current_stream()
     return ctypes.c_void_p(s.cuda_stream)
+
+
+# Batches of more rows than this are offered scratch memory (the library says how much it can use).
+_SCRATCH_MIN_M = 112
+
+
+def _scratch(need: int, device, stream) -> torch.Tensor | None:
+    """`need` bytes from the caching allocator for one call on `stream`: a block of that stream's own pool, so it
+    is reused only behind the call.  None where none is needed or free (the call then runs without)."""
+    if need <= 0:
+        return None
+    try:
+        if stream is None or stream.cuda_stream == torch.cuda.current_stream().cuda_stream:
+            return torch.empty((need,), dtype=torch.uint8, device=device)
+        if not isinstance(stream, torch.cuda.Stream):
+            stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+        with torch.cuda.stream(stream):
+            return torch.empty((need,), dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
 
 
 def _dev_tensor(t: torch.Tensor, name: str) -> torch.Tensor:
@@ -338,9 +366,20 @@ def sparse_linear(X: torch.Tensor, Wc: SparseMatrix, out: torch.Tensor | None = 
     _arg(out, "out", shape=(M, Wc.rows), dtype=Wc.dtype)
     _dev_tensor(X, "X")
     view = Wc.view()
+    if algo == "auto" and M > _SCRATCH_MIN_M:
+        _linear_group(L, (_SparseTask * 1)(_SparseTask(X.data_ptr(), ctypes.pointer(view), out.data_ptr())), 1, M,
+                      X.device, stream)
+        return out
     _check("spl_sparse_linear_ex", L.spl_sparse_linear_ex(_ptr(X), M, ctypes.byref(view), _ptr(out), ALGO[algo],
                                                           _stream(stream)))
     return out
+
+
+def _linear_group(L, tasks, n: int, M: int, device, stream) -> None:
+    """AUTO on a task array, with scratch."""
+    ws = _scratch(L.spl_sparse_linear_group_scratch_bytes(tasks, n, M), device, stream)
+    _check("spl_sparse_linear_group_scratch",
+           L.spl_sparse_linear_group_scratch(tasks, n, M, _ptr(ws), 0 if ws is None else ws.numel(), _stream(stream)))
 
 
 def sparse_linear_expanded(X: torch.Tensor, Wc: SparseMatrix, out: torch.Tensor | None = None,
@@ -382,6 +421,13 @@ def sparse_linear_silu_mul(X: torch.Tensor, Wgate: SparseMatrix, Wup: SparseMatr
     _arg(out, "out", shape=(M, Wgate.rows), dtype=Wgate.dtype)
     _dev_tensor(X, "X")
     vg, vu = Wgate.view(), Wup.view()
+    if algo == "auto" and M > _SCRATCH_MIN_M:
+        ws = _scratch(L.spl_sparse_linear_silu_mul_scratch_bytes(M, ctypes.byref(vg), ctypes.byref(vu)), X.device,
+                      stream)
+        _check("spl_sparse_linear_silu_mul_scratch",
+               L.spl_sparse_linear_silu_mul_scratch(_ptr(X), M, ctypes.byref(vg), ctypes.byref(vu), _ptr(out),
+                                                    _ptr(ws), 0 if ws is None else ws.numel(), _stream(stream)))
+        return out
     _check("spl_sparse_linear_silu_mul", L.spl_sparse_linear_silu_mul(_ptr(X), M, ctypes.byref(vg), ctypes.byref(vu),
                                                                       _ptr(out), ALGO[algo], _stream(stream)))
     return out
@@ -533,6 +579,13 @@ def sparse_input_grad(dY: torch.Tensor, Wc: SparseMatrix, out: torch.Tensor | No
         out = torch.empty((M, Wc.cols), dtype=dY.dtype, device=dY.device)
     _dev_tensor(out, "out")
     view = Wc.view()
+    if workspace is None:
+        ws = _scratch(L.spl_sparse_input_grad_scratch_bytes(M, ctypes.byref(view)), dY.device, stream)
+        if ws is not None:
+            _check("spl_sparse_input_grad_scratch",
+                   L.spl_sparse_input_grad_scratch(_ptr(dY), M, ctypes.byref(view), _ptr(out), _ptr(ws), ws.numel(),
+                                                   _stream(stream)))
+            return out
     need = L.spl_sparse_input_grad_workspace_bytes(M, ctypes.byref(view))
     if need < 0:
         raise ValueError("spl_sparse_input_grad_workspace_bytes rejected the shape")
@@ -643,10 +696,22 @@ def sparse_linear_int8(Xq: torch.Tensor, x_scales: torch.Tensor, Wqc: SparseMatr
     _q_outs(out, acc_out, M, Wqc.rows)
     _q_args(Xq, x_scales, Wqc.rows, Wqc.cols, w_scales, M)
     view = Wqc.view()
+    if M > _SCRATCH_MIN_M:
+        task = _Int8Task(Xq.data_ptr(), x_scales.data_ptr(), ctypes.pointer(view), w_scales.data_ptr(),
+                         out.data_ptr(), None if acc_out is None else acc_out.data_ptr())
+        _int8_group(L, (_Int8Task * 1)(task), 1, M, Xq.device, stream)
+        return out
     _check("spl_sparse_linear_int8", L.spl_sparse_linear_int8(_ptr(Xq), _ptr(x_scales), M, ctypes.byref(view),
                                                               _ptr(w_scales), _ptr(out), _ptr(acc_out),
                                                               _stream(stream)))
     return out
+
+
+def _int8_group(L, tasks, n: int, M: int, device, stream) -> None:
+    ws = _scratch(L.spl_sparse_linear_int8_group_scratch_bytes(tasks, n, M), device, stream)
+    _check("spl_sparse_linear_int8_group_scratch",
+           L.spl_sparse_linear_int8_group_scratch(tasks, n, M, _ptr(ws), 0 if ws is None else ws.numel(),
+                                                  _stream(stream)))
 
 
 def sparse_linear_int8_expanded(Xq: torch.Tensor, x_scales: torch.Tensor, Wqc: SparseMatrix, w_scales: torch.Tensor,
@@ -740,6 +805,9 @@ def sparse_linear_group(Xs, Wcs, outs=None, algo: str = "auto", stream=None):
         tasks[i].X = X.data_ptr()
         tasks[i].W = ctypes.pointer(views[i])
         tasks[i].Y = Y.data_ptr()
+    if algo == "auto" and M > _SCRATCH_MIN_M:
+        _linear_group(L, tasks, n, M, Xs[0].device, stream)
+        return outs
     _check("spl_sparse_linear_group", L.spl_sparse_linear_group(tasks, n, M, ALGO[algo], _stream(stream)))
     return outs
 
@@ -800,6 +868,9 @@ def sparse_linear_int8_group(Xqs, x_scales, Wqcs, w_scales, outs=None, acc_outs=
         tasks[i].Wq = ctypes.pointer(views[i])
         tasks[i].w_scales, tasks[i].Y = w_scales[i].data_ptr(), outs[i].data_ptr()
         tasks[i].acc_out = None if accs[i] is None else accs[i].data_ptr()
+    if M > _SCRATCH_MIN_M:
+        _int8_group(L, tasks, n, M, Xqs[0].device, stream)
+        return outs
     _check("spl_sparse_linear_int8_group", L.spl_sparse_linear_int8_group(tasks, n, M, _stream(stream)))
     return outs
 

@@ -36,9 +36,6 @@ constexpr int kI8VBufAlloc = kI8VBuf + 16;  // + room past the last window
 constexpr int kI8PieceRounds = kI8VBuf / 16 / kWave;
 constexpr int kI8XLdsMax = 32 * 1024;       // activations staged in LDS when M * 64 ceil(S/2) bytes fit
 constexpr int kI8OffsetLanes = kWave - 1;
-// Batches from this size on use the prefill kernels' MFMA tiling (activations staged in LDS and
-// shared by the row blocks of a workgroup) instead of the streaming kernels below.
-constexpr int64_t kI8PrefillMinM = 128;
 // Batches of more rows than one batch fragment go to the streaming kernel that stages activations through
 // LDS, where it can address them: per launch, this file's kernel / that one, q|k|v 13.9 / 14.4 us at 16
 // rows, 20.4 / 18.7 at 32, 55.1 / 32.2 at 127; gate|up 21.1 / 28.3, 34.6 / 30.9, 95.6 / 61.0.

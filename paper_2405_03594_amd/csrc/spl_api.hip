@@ -268,6 +268,79 @@ spl_status spl_sparse_linear_group(const spl_sparse_task* tasks, int32_t count, 
   return SPL_OK;
 }
 
+// AUTO with scratch: batches past the streaming kernel go through decoded
+// fragments.  The arguments are checked as by the plain calls.
+static bool usable(const void* scratch, int64_t have, int64_t need) {
+  return need > 0 && scratch && have >= need && aligned(scratch, 256);
+}
+
+static int64_t linear_scratch(const spl_sparse_task* tasks, int32_t count, int64_t M) {
+  const spl_matrix* W[SPL_MAX_GROUP];
+  if (M <= spl::kWideMaxM) return 0;
+  for (int32_t i = 0; i < count; ++i) W[i] = tasks[i].W;
+  return spl::frag_linear_bytes(W, count, M);
+}
+
+static spl_status check_sparse_group(const spl_sparse_task* tasks, int32_t count, int64_t M) {
+  if (!tasks || count < 1 || count > SPL_MAX_GROUP || M < 0) return SPL_ERR_INVALID_ARG;
+  int64_t blocks = 0;
+  for (int32_t i = 0; i < count; ++i) {
+    int32_t a = SPL_ALGO_AUTO;
+    const spl_status st = check_sparse_task(tasks[i].X, M, tasks[i].W, tasks[i].Y, &a);
+    if (st != SPL_OK) return st;
+    if (tasks[i].W->dtype != tasks[0].W->dtype) return SPL_ERR_INVALID_ARG;
+    blocks += spl::tile_blocks(tasks[i].W->rows);
+  }
+  return blocks >= kMaxDim ? SPL_ERR_OVERFLOW : SPL_OK;
+}
+
+int64_t spl_sparse_linear_group_scratch_bytes(const spl_sparse_task* tasks, int32_t count, int64_t M) {
+  if (check_sparse_group(tasks, count, M) != SPL_OK) return -1;
+  return linear_scratch(tasks, count, M);
+}
+
+spl_status spl_sparse_linear_group_scratch(const spl_sparse_task* tasks, int32_t count, int64_t M, void* scratch,
+                                           int64_t scratch_bytes, hipStream_t stream) {
+  const spl_status st = check_sparse_group(tasks, count, M);
+  if (st != SPL_OK) return st;
+  if (!usable(scratch, scratch_bytes, linear_scratch(tasks, count, M)))
+    return spl_sparse_linear_group(tasks, count, M, SPL_ALGO_AUTO, stream);
+  (void)hipGetLastError();
+  return launched(spl::launch_frag_linear(tasks, count, M, scratch, stream));
+}
+
+static int64_t gated_scratch(int64_t M, const spl_matrix* Wgate, const spl_matrix* Wup) {
+  if (M <= kGatedWideMaxM) return 0;
+  const spl_matrix* W[2] = {Wgate, Wup};
+  return spl::frag_linear_bytes(W, 2, M);
+}
+
+int64_t spl_sparse_linear_silu_mul_scratch_bytes(int64_t M, const spl_matrix* Wgate, const spl_matrix* Wup) {
+  for (const spl_matrix* W : {Wgate, Wup})
+    if (!W || M < 0 || spl_check_matrix(W) != SPL_OK || !fp_dtype(W->dtype) || W->layout != SPL_LAYOUT_TILE16 ||
+        W->cols % 8 != 0 || (M > 0 && (!dims_ok(M, W->rows) || !dims_ok(M, W->cols))))
+      return -1;
+  if (Wup->dtype != Wgate->dtype || Wup->rows != Wgate->rows || Wup->cols != Wgate->cols) return -1;
+  return gated_scratch(M, Wgate, Wup);
+}
+
+spl_status spl_sparse_linear_silu_mul_scratch(const void* X, int64_t M, const spl_matrix* Wgate,
+                                              const spl_matrix* Wup, void* Y, void* scratch, int64_t scratch_bytes,
+                                              hipStream_t stream) {
+  if (!Wgate || !Wup || M < 0) return SPL_ERR_INVALID_ARG;
+  int32_t a = SPL_ALGO_AUTO;
+  spl_status st = check_sparse_task(X, M, Wgate, Y, &a);
+  if (st != SPL_OK) return st;
+  a = SPL_ALGO_AUTO;
+  st = check_sparse_task(X, M, Wup, Y, &a);
+  if (st != SPL_OK) return st;
+  if (Wup->dtype != Wgate->dtype || Wup->rows != Wgate->rows || Wup->cols != Wgate->cols) return SPL_ERR_INVALID_ARG;
+  if (!usable(scratch, scratch_bytes, gated_scratch(M, Wgate, Wup)))
+    return spl_sparse_linear_silu_mul(X, M, Wgate, Wup, Y, SPL_ALGO_AUTO, stream);
+  (void)hipGetLastError();
+  return launched(spl::launch_frag_gated(X, M, *Wgate, *Wup, Y, scratch, stream));
+}
+
 spl_status spl_sparse_linear(const void* X, int64_t M, const spl_matrix* Wc, void* Y, hipStream_t stream) {
   return spl_sparse_linear_ex(X, M, Wc, Y, SPL_ALGO_AUTO, stream);
 }
@@ -426,6 +499,25 @@ spl_status spl_sparse_input_grad(const void* dY, int64_t M, const spl_matrix* Wc
   return launched(spl::launch_input_grad(dY, M, *Wc, dX, workspace, stream));
 }
 
+int64_t spl_sparse_input_grad_scratch_bytes(int64_t M, const spl_matrix* Wc) {
+  if (check_tiled_fp(Wc) != SPL_OK || M < 0) return -1;
+  if (M > 0 && (!dims_ok(M, Wc->rows) || !dims_ok(M, Wc->cols))) return -1;
+  return M == 0 ? 0 : spl::frag_input_grad_bytes(*Wc, M);
+}
+
+spl_status spl_sparse_input_grad_scratch(const void* dY, int64_t M, const spl_matrix* Wc, void* dX, void* scratch,
+                                         int64_t scratch_bytes, hipStream_t stream) {
+  const spl_status st = check_tiled_fp(Wc);
+  if (st != SPL_OK) return st;
+  const spl_status xy = check_xy(dY, M, Wc->rows, Wc->cols, dX);   // dY [M][N], dX [M][K]
+  if (xy != SPL_OK || M == 0) return xy;
+  if (!usable(scratch, scratch_bytes, spl::frag_input_grad_bytes(*Wc, M)))
+    return spl::sparse_input_grad_applies(M, *Wc) ? spl_sparse_input_grad(dY, M, Wc, dX, nullptr, stream)
+                                                  : SPL_ERR_UNSUPPORTED;
+  (void)hipGetLastError();
+  return launched(spl::launch_frag_input_grad(dY, M, *Wc, dX, scratch, stream));
+}
+
 spl_status spl_sparse_sgd_update(const spl_matrix* Wc, const void* grad_values, float lr, hipStream_t stream) {
   const spl_status st = check_tiled_fp(Wc);
   if (st != SPL_OK) return st;
@@ -540,7 +632,14 @@ spl_status spl_sparse_linear_int8_expanded(const int8_t* Xq, const float* x_scal
   return launched(spl::launch_dense_prefill_i8(d, M, stream));
 }
 
-spl_status spl_sparse_linear_int8_group(const spl_int8_task* tasks, int32_t count, int64_t M, hipStream_t stream) {
+static int64_t int8_scratch(const spl_int8_task* tasks, int32_t count, int64_t M) {
+  const spl_matrix* W[SPL_MAX_GROUP];
+  if (M < spl::kI8PrefillMinM) return 0;
+  for (int32_t i = 0; i < count; ++i) W[i] = tasks[i].Wq;
+  return spl::frag_linear_bytes(W, count, M);
+}
+
+static spl_status check_int8_group(const spl_int8_task* tasks, int32_t count, int64_t M) {
   if (!tasks || count < 1 || count > SPL_MAX_GROUP || M < 0) return SPL_ERR_INVALID_ARG;
   int64_t blocks = 0;
   for (int32_t i = 0; i < count; ++i) {
@@ -548,10 +647,29 @@ spl_status spl_sparse_linear_int8_group(const spl_int8_task* tasks, int32_t coun
     if (st != SPL_OK) return st;
     blocks += spl::tile_blocks(tasks[i].Wq->rows);
   }
-  if (blocks >= kMaxDim || M >= kMaxDim) return SPL_ERR_OVERFLOW;
-  if (M == 0) return SPL_OK;
+  return blocks >= kMaxDim || M >= kMaxDim ? SPL_ERR_OVERFLOW : SPL_OK;
+}
+
+spl_status spl_sparse_linear_int8_group(const spl_int8_task* tasks, int32_t count, int64_t M, hipStream_t stream) {
+  const spl_status st = check_int8_group(tasks, count, M);
+  if (st != SPL_OK || M == 0) return st;
   (void)hipGetLastError();
   return launched(spl::launch_sparse_int8(tasks, count, M, stream));
+}
+
+int64_t spl_sparse_linear_int8_group_scratch_bytes(const spl_int8_task* tasks, int32_t count, int64_t M) {
+  if (check_int8_group(tasks, count, M) != SPL_OK) return -1;
+  return int8_scratch(tasks, count, M);
+}
+
+spl_status spl_sparse_linear_int8_group_scratch(const spl_int8_task* tasks, int32_t count, int64_t M, void* scratch,
+                                                int64_t scratch_bytes, hipStream_t stream) {
+  const spl_status st = check_int8_group(tasks, count, M);
+  if (st != SPL_OK) return st;
+  if (!usable(scratch, scratch_bytes, int8_scratch(tasks, count, M)))
+    return spl_sparse_linear_int8_group(tasks, count, M, stream);
+  (void)hipGetLastError();
+  return launched(spl::launch_frag_int8(tasks, count, M, scratch, stream));
 }
 
 spl_status spl_dense_linear_ex(const void* X, int64_t M, const void* W, int32_t dtype, int64_t N, int64_t K,
@@ -565,7 +683,6 @@ spl_status spl_dense_linear_group(const spl_dense_task* tasks, int32_t count, in
   if (!tasks || count < 1 || count > SPL_MAX_GROUP || M < 0) return SPL_ERR_INVALID_ARG;
   int64_t blocks = 0;
   int32_t resolved = algo;
-  bool wide = algo == SPL_ALGO_AUTO && M > kStreamMaxM;
   for (int32_t i = 0; i < count; ++i) {
     int32_t a = algo;
     const spl_status st = check_dense_task(&tasks[i], M, dtype, &a);
