@@ -14,7 +14,7 @@ constexpr int64_t kMaxDim = (int64_t)1 << 31;        // N, K, M < 2^31
 constexpr int64_t kMaxElems = (int64_t)1 << 40;      // N * K, M * K, M * N
 constexpr int64_t kDecodeMaxM = 32;
 constexpr int64_t kGatedDecodeMaxM = 16;           // the paired decode kernel holds one 16-row batch tile
-// AUTO: the decode kernel up to this many rows, then the streaming kernel of
+// AUTO: the one-row kernel up to this many rows, then the streaming kernel of
 // several batch fragments as far as it goes (spl::kWideMaxM; the gated half:
 // kGatedWideMaxM), then the prefill kernels.
 constexpr int64_t kStreamMaxM = 1;
@@ -260,6 +260,8 @@ spl_status spl_sparse_linear_group(const spl_sparse_task* tasks, int32_t count, 
   if (M == 0) return SPL_OK;
   (void)hipGetLastError();
   if (wide) return launched(spl::launch_sparse_wide(tasks, count, M, stream));
+  if (algo == SPL_ALGO_AUTO && M <= kStreamMaxM && resolved == SPL_ALGO_DECODE)
+    return launched(spl::launch_sparse_row(tasks, count, stream));
   if (resolved == SPL_ALGO_DECODE) return launched(spl::launch_sparse_decode(tasks, count, M, stream));
   for (int32_t i = 0; i < count; ++i) {
     const spl_status st = launched(spl::launch_sparse_prefill(tasks[i].X, M, *tasks[i].W, tasks[i].Y, stream));
@@ -360,6 +362,8 @@ spl_status spl_sparse_linear_silu_mul(const void* X, int64_t M, const spl_matrix
   if (2 * spl::tile_blocks(Wgate->rows) >= kMaxDim) return SPL_ERR_OVERFLOW;
   if (M == 0) return SPL_OK;
   (void)hipGetLastError();
+  if (algo == SPL_ALGO_AUTO && M <= kStreamMaxM && ag == SPL_ALGO_DECODE)
+    return launched(spl::launch_gated_row(X, *Wgate, *Wup, Y, stream));
   if (algo == SPL_ALGO_AUTO && M <= kGatedWideMaxM && spl::sparse_wide_fits(M, Wgate->cols, 2))
     return launched(spl::launch_gated_wide(X, M, *Wgate, *Wup, Y, stream));
   if (ag == SPL_ALGO_DECODE) return launched(spl::launch_gated_decode(X, M, *Wgate, *Wup, Y, stream));

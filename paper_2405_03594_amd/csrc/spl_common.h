@@ -203,6 +203,9 @@ hipError_t launch_zero_fill(void* Y, int64_t count16, hipStream_t s);
 // Decode kernels over a group of 1..SPL_MAX_GROUP validated tasks (one launch).
 hipError_t launch_sparse_decode(const spl_sparse_task* tasks, int count, int64_t M, hipStream_t s);
 hipError_t launch_dense_decode(const spl_dense_task* tasks, int count, int64_t M, int32_t dtype, hipStream_t s);
+// One activation row of up to 2^30 columns: groups of 1..SPL_MAX_GROUP validated tasks, the gated half of an MLP.
+hipError_t launch_sparse_row(const spl_sparse_task* tasks, int count, hipStream_t s);
+hipError_t launch_gated_row(const void* X, const spl_matrix& Wg, const spl_matrix& Wu, void* Y, hipStream_t s);
 // Streaming kernel for batches of up to kWideMaxM rows whose activations
 // (`bytes` each) it can address: groups of 1..SPL_MAX_GROUP validated tasks,
 // the gated half of an MLP, int8 groups.
