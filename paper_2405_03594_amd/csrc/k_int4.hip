@@ -206,6 +206,8 @@ hipError_t launch_sparse_int4(const int8_t* Xq, const float* sx, int64_t M, cons
                               void* Y, int32_t* acc_out, hipStream_t s) {
   // the kernel addresses X, a row block's words and its tile offsets with 32-bit buffer offsets
   if (M * W4.cols >= (int64_t)1 << 31 || tile_steps(W4.cols) >= (int64_t)1 << 25) return hipErrorNotSupported;
+  // four tiles per scan, where 16 x the sums of a wave's columns stay in 32 bits
+  if (W4.cols <= kInt4QuadMaxK) return launch_int4_quad(Xq, sx, M, W4, sw, Y, acc_out, s);
   I4Args g{Xq, sx, W4.bitmask, static_cast<const uint8_t*>(W4.values), W4.tile_offsets, sw,
            static_cast<uint16_t*>(Y), acc_out, W4.rows, W4.cols, (int32_t)M};
   const int64_t blocks = tile_blocks(W4.rows);

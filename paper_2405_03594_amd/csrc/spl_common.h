@@ -292,6 +292,11 @@ int64_t int4_values_bytes(int64_t nnz);
 hipError_t launch_pack_nibbles(const int8_t* v8, int64_t nnz, uint8_t* v4, int32_t* bad, hipStream_t s);
 hipError_t launch_sparse_int4(const int8_t* Xq, const float* sx, int64_t M, const spl_matrix& W4, const float* sw,
                               void* Y, int32_t* acc_out, hipStream_t s);
+// The same by quads of tiles: M <= 16, M K < 2^31, K <= kInt4QuadMaxK (its sums are 16 x the codes': a wave of at
+// least 8 multiplies (2^20 / 8 + 128) columns, half of them per accumulator, 2^14 at most each).
+constexpr int64_t kInt4QuadMaxK = (int64_t)1 << 20;
+hipError_t launch_int4_quad(const int8_t* Xq, const float* sx, int64_t M, const spl_matrix& W4, const float* sw,
+                            void* Y, int32_t* acc_out, hipStream_t s);
 // Streaming-read probe over `bytes` (a multiple of 16) of a 16-byte aligned buffer.
 hipError_t launch_read_probe(const void* buf, int64_t bytes, uint32_t* sink, int cus, hipStream_t s);
 hipError_t launch_quantize_rows_i8(const void* X, int32_t dtype, int64_t M, int64_t K, int8_t* Xq, float* sx,
