@@ -297,6 +297,9 @@ hipError_t launch_sparse_int4(const int8_t* Xq, const float* sx, int64_t M, cons
 constexpr int64_t kInt4QuadMaxK = (int64_t)1 << 20;
 hipError_t launch_int4_quad(const int8_t* Xq, const float* sx, int64_t M, const spl_matrix& W4, const float* sw,
                             void* Y, int32_t* acc_out, hipStream_t s);
+// int8 groups of up to 16 rows whose activations and words it can address.
+inline bool int8_quad_fits(int64_t M, int64_t K) { return M * K < (int64_t)1 << 31 && K <= (int64_t)1 << 29; }
+hipError_t launch_int8_quad(const spl_int8_task* tasks, int count, int64_t M, hipStream_t s);
 // Streaming-read probe over `bytes` (a multiple of 16) of a 16-byte aligned buffer.
 hipError_t launch_read_probe(const void* buf, int64_t bytes, uint32_t* sink, int cus, hipStream_t s);
 hipError_t launch_quantize_rows_i8(const void* X, int32_t dtype, int64_t M, int64_t K, int8_t* Xq, float* sx,

@@ -44,7 +44,7 @@ def test_int4_quad(orc, spl, N, K, s):
     W4 = _pack4(spl, Wq, mask)
     Xq, sx = synth.int8_activations(931 + K, 16, K)
     p = orc.pack(Wq, "i8", mask)
-    for M in (1, 2, 9, 16):
+    for M in (1, 4, 5, 9, 16):
         acc_ref, y_ref = orc.linear_i8(Xq[:M], sx[:M], p, sw)
         acc, y = _run(spl, Xq[:M], sx[:M], W4, sw, N)
         _assert_equal(acc, acc_ref, f"acc N={N} K={K} s={s} M={M}")
