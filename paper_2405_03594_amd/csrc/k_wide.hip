@@ -480,7 +480,9 @@ hipError_t launch_sparse_wide(const spl_sparse_task* tasks, int count, int64_t M
   for (int i = 0; i < count; ++i) {
     const spl_matrix& W = *tasks[i].W;
     if (!sparse_wide_fits(M, W.cols, 2)) return hipErrorNotSupported;
-    if (W.nnz == 0) {                                // nothing kept: +0
+    // Nothing kept: +0 above the decode kernels' 32 rows, as in the prefill kernels; up to there the product is
+    // computed, as at one row (activations that are not finite give NaN).
+    if (W.nnz == 0 && M > 32) {
       const hipError_t e = launch_zero_fill(tasks[i].Y, M * W.rows, s);
       if (e != hipSuccess) return e;
     } else {
