@@ -95,7 +95,7 @@ __global__ void __launch_bounds__(W * kWave, W == 16 ? 4 : 6) k_sparse_row(const
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, fr = lane & 15, fg = lane >> 4;
   const int ti = kGated ? wave / WK : find_task(g.first, g.count);
-  const RowTaskArg tk = g.t[ti];                     // (2 K < 2^31 bytes of activations: the launcher's caller checks)
+  const RowTaskArg tk = g.t[ti];                     // (at most 2^31 bytes of activations: the launchers check)
   const int64_t K = tk.K;
   const int64_t blk = kGated ? (int64_t)blockIdx.x : (int64_t)blockIdx.x - g.first[ti];
   const int S = (int)tile_steps(K);
@@ -107,11 +107,11 @@ __global__ void __launch_bounds__(W * kWave, W == 16 ? 4 : 6) k_sparse_row(const
     if (kbeg > kend) kbeg = kend;
   }
   const int32_t* tob = tk.toff + blk * S;
-  const auto rsrc = [](const void* p, int bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000);
+  const auto rsrc = [](const void* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
   };
-  const __amdgpu_buffer_rsrc_t bm_rsrc = rsrc(tk.bm + blk * S * 16, 64 * kend);   // tiles past the range read zeros
-  const __amdgpu_buffer_rsrc_t x_rsrc = rsrc(tk.X, (int)(2 * K));                 // columns past K too
+  const __amdgpu_buffer_rsrc_t bm_rsrc = rsrc(tk.bm + blk * S * 16, 64u * (uint32_t)kend);   // past the range: zeros
+  const __amdgpu_buffer_rsrc_t x_rsrc = rsrc(tk.X, (uint32_t)(2 * K));                       // columns past K too
 
   u32x2* lut = reinterpret_cast<u32x2*>(dsm + wave * kRowWaveLds);
   unsigned char* slot = dsm + wave * kRowWaveLds + kRowTable;
@@ -148,7 +148,7 @@ __global__ void __launch_bounds__(W * kWave, W == 16 ? 4 : 6) k_sparse_row(const
     const uint32_t n8 = (2u * o8 - a0 + 15u) >> 4;
     two = c0 + 4 < kend && n8 <= (uint32_t)kRowPieces;   // (a quad past the range has activations, and 0 x inf)
     np = (int)(two ? n8 : (2u * o4 - a0 + 15u) >> 4);
-    const __amdgpu_buffer_rsrc_t v_rsrc = rsrc(tk.values + a0, 16 * np);
+    const __amdgpu_buffer_rsrc_t v_rsrc = rsrc(tk.values + a0, 16u * (uint32_t)np);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (i == 0 || np > kWave * i)                  // wave-uniform
@@ -301,6 +301,9 @@ hipError_t row_pick(const RowGroupArg& g, hipStream_t s) {
   return blocks < 4 * cus || kGated ? row_launch<T, 8, kGated>(g, s) : row_launch<T, 4, kGated>(g, s);
 }
 
+// A row's activations, and a row block's words, are addressed with 32-bit byte offsets.
+constexpr int64_t kRowMaxK = (int64_t)1 << 30;
+
 RowTaskArg row_task(const void* X, const spl_matrix& W, void* Y) {
   return RowTaskArg{static_cast<const uint16_t*>(X), static_cast<uint16_t*>(Y),   W.bitmask,
                     static_cast<const unsigned char*>(W.values), W.tile_offsets, W.rows, W.cols};
@@ -312,6 +315,7 @@ hipError_t launch_sparse_row(const spl_sparse_task* tasks, int count, hipStream_
   RowGroupArg g{};
   g.count = count;
   for (int i = 0; i < count; ++i) {
+    if (tasks[i].W->cols > kRowMaxK) return hipErrorNotSupported;
     g.t[i] = row_task(tasks[i].X, *tasks[i].W, tasks[i].Y);
     g.first[i + 1] = g.first[i] + (int32_t)tile_blocks(tasks[i].W->rows);
   }
@@ -319,6 +323,7 @@ hipError_t launch_sparse_row(const spl_sparse_task* tasks, int count, hipStream_
 }
 
 hipError_t launch_gated_row(const void* X, const spl_matrix& Wg, const spl_matrix& Wu, void* Y, hipStream_t s) {
+  if (Wg.cols > kRowMaxK) return hipErrorNotSupported;
   if (Wg.nnz == 0 || Wu.nnz == 0) return launch_zero_fill(Y, Wg.rows, s);   // silu(0) u = silu(g) 0 = 0
   RowGroupArg g{};
   g.t[0] = row_task(X, Wg, Y);

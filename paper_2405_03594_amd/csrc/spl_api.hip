@@ -252,7 +252,7 @@ spl_status spl_sparse_linear_group(const spl_sparse_task* tasks, int32_t count, 
     const spl_status st = check_sparse_task(tasks[i].X, M, tasks[i].W, tasks[i].Y, &a);
     if (st != SPL_OK) return st;
     if (tasks[i].W->dtype != tasks[0].W->dtype) return SPL_ERR_INVALID_ARG;
-    resolved = a;                                      // AUTO depends on M only: the same for every task
+    resolved = a;                                      // (the launchers refuse a group that another task does not fit)
     wide = wide && spl::sparse_wide_fits(M, tasks[i].W->cols, 2);
     blocks += spl::tile_blocks(tasks[i].W->rows);
   }

@@ -241,6 +241,11 @@ def test_group_argument_checks(L):
     assert f(tasks(m), 1, -1, 0, None) == INVALID
     assert f(tasks(m), 1, 33, 1, None) == UNSUPPORTED             # decode family is M <= 32
 
+    # one row: the kernels address an activation row with 32-bit byte offsets, whichever task of a group is too long
+    long = _mat(layout=1, tile_offsets=0x40000, cols=(1 << 30) + 64)
+    assert f(tasks(long, m), 2, 1, 0, None) == UNSUPPORTED
+    assert f(tasks(long, m), 2, 2, 0, None) == UNSUPPORTED
+
     g = L.spl_dense_linear_group
     d = (_DenseTask * 2)()
     for i in range(2):
