@@ -574,25 +574,28 @@ hipError_t fg_product(FgGroupArg& g, hipStream_t s) {
 }
 
 // A product of M rows with a decoded rows x cols matrix is addressable: its
-// fragments and a workgroup's activations with 32-bit byte offsets, its tiles
-// with 32-bit workgroup numbers.
+// fragments and a workgroup's activations with 32-bit byte offsets.
 template <bool kQ>
 bool fg_fits(int64_t M, int64_t rows, int64_t cols) {
   return M >= 1 && M < ((int64_t)1 << 31) && cols <= ((int64_t)1 << 21) &&
-         fg_bytes<kQ>(rows, cols) < ((int64_t)1 << 31) &&
-         tile_blocks(rows) * ((M + 127) / 128) < ((int64_t)1 << 26);
+         fg_bytes<kQ>(rows, cols) < ((int64_t)1 << 31);
 }
+// Workgroups of a task in the smallest tiles (64 x 128, 256 threads); a launch
+// of them all stays below 2^32 threads up to kFgMaxGroups.
+constexpr int64_t kFgMaxGroups = ((int64_t)1 << 24) - 1;
+int64_t fg_groups(int64_t M, int64_t rows) { return ((rows + 63) / 64) * ((M + 127) / 128); }
 
 }  // namespace
 
 int64_t frag_linear_bytes(const spl_matrix* const* W, int count, int64_t M) {
-  int64_t bytes = 0;
+  int64_t bytes = 0, groups = 0;
   for (int i = 0; i < count; ++i) {
     const bool q = W[i]->dtype == SPL_I8;
+    groups += fg_groups(M, W[i]->rows);
     if (!(q ? fg_fits<true>(M, W[i]->rows, W[i]->cols) : fg_fits<false>(M, W[i]->rows, W[i]->cols))) return 0;
     if (W[i]->nnz > 0) bytes += q ? fg_bytes<true>(W[i]->rows, W[i]->cols) : fg_bytes<false>(W[i]->rows, W[i]->cols);
   }
-  return bytes;
+  return groups <= kFgMaxGroups ? bytes : 0;
 }
 
 hipError_t launch_frag_linear(const spl_sparse_task* tasks, int count, int64_t M, void* scratch, hipStream_t s) {
@@ -662,7 +665,8 @@ hipError_t launch_frag_int8(const spl_int8_task* tasks, int count, int64_t M, vo
 
 // dX [M][K] = dY [M][N] W: the product with W transposed, decoded as such.
 int64_t frag_input_grad_bytes(const spl_matrix& W, int64_t M) {
-  if (W.rows % 8 != 0 || !fg_fits<false>(M, 32 * tile_steps(W.cols), W.rows)) return 0;
+  if (W.rows % 8 != 0 || !fg_fits<false>(M, 32 * tile_steps(W.cols), W.rows) || fg_groups(M, W.cols) > kFgMaxGroups)
+    return 0;
   return 2 * tile_steps(W.cols) * fg_steps<false>(W.rows) * 1024;
 }
 

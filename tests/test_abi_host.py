@@ -246,6 +246,11 @@ def test_group_argument_checks(L):
     assert f(tasks(long, m), 2, 1, 0, None) == UNSUPPORTED
     assert f(tasks(long, m), 2, 2, 0, None) == UNSUPPORTED
 
+    # scratch: none offered where the decoded product's launch would pass 2^32 threads (batches far larger than N)
+    size = L.spl_sparse_linear_group_scratch_bytes
+    assert size(tasks(*([m] * MAX_GROUP)), MAX_GROUP, 1 << 20) > 0
+    assert size(tasks(*([m] * MAX_GROUP)), MAX_GROUP, 1 << 29) == 0
+
     g = L.spl_dense_linear_group
     d = (_DenseTask * 2)()
     for i in range(2):
