@@ -177,17 +177,18 @@ _SCRATCH_MIN_M = 112
 
 
 def _scratch(need: int, device, stream) -> torch.Tensor | None:
-    """`need` bytes from the caching allocator for one call on `stream`: a block of that stream's own pool, so it
-    is reused only behind the call.  None where none is needed or free (the call then runs without)."""
+    """`need` bytes from the caching allocator for one call on `stream` (None: the current one): a block of that
+    stream's own pool, so it is reused only behind the call.  `device` is that of a stream known by its handle
+    alone.  None where none is needed or free (the call then runs without)."""
     if need <= 0:
         return None
     try:
-        if stream is None or stream.cuda_stream == torch.cuda.current_stream().cuda_stream:
-            return torch.empty((need,), dtype=torch.uint8, device=device)
-        if not isinstance(stream, torch.cuda.Stream):
+        if stream is not None and not isinstance(stream, torch.cuda.Stream):
             stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+        if stream is None or stream == torch.cuda.current_stream():
+            return torch.empty((need,), dtype=torch.uint8, device="cuda")
         with torch.cuda.stream(stream):
-            return torch.empty((need,), dtype=torch.uint8, device=device)
+            return torch.empty((need,), dtype=torch.uint8, device=stream.device)
     except torch.OutOfMemoryError:
         return None
 

@@ -539,3 +539,54 @@ def test_wrappers_reject_mismatched_tensors_before_any_launch():
     for fn, what in cases:
         with pytest.raises(ValueError, match=what):
             fn()
+
+
+def test_scratch_belongs_to_the_stream_of_the_call(monkeypatch):
+    """Scratch comes from the pool of the stream that the kernels run on.  Default streams of two devices have the
+    same handle: a call on the other device's must not take a block of whatever stream is current there."""
+    import contextlib
+
+    import torch
+
+    import paper_2405_03594_amd as spl
+
+    class Stream:
+        def __init__(self, device, handle):
+            self.device, self.cuda_stream = torch.device("cuda", device), handle
+
+        def __eq__(self, other):
+            return (self.device, self.cuda_stream) == (other.device, other.cuda_stream)
+
+    class Handle:                                       # any object that has a stream's handle
+        cuda_stream = 64
+
+    entered, got = [], []
+
+    @contextlib.contextmanager
+    def stream(s):
+        entered.append(s)
+        yield
+        entered.pop()
+
+    class External(Stream):
+        def __init__(self, handle, device):
+            super().__init__(device.index, handle)
+
+    def empty(shape, dtype, device):
+        got.append((entered[-1] if entered else None, torch.device(device)))
+        return shape
+
+    current = Stream(0, 0)
+    monkeypatch.setattr(torch.cuda, "Stream", Stream)
+    monkeypatch.setattr(torch.cuda, "ExternalStream", External)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: current)
+    monkeypatch.setattr(torch.cuda, "stream", stream)
+    monkeypatch.setattr(torch, "empty", empty)
+    d0, d1 = torch.device("cuda", 0), torch.device("cuda", 1)
+    other, side = Stream(1, 0), Stream(0, 32)
+    assert spl._scratch(0, d0, None) is None and not got
+    for device, s, want in ((d0, None, (None, torch.device("cuda"))), (d0, Stream(0, 0), (None, torch.device("cuda"))),
+                            (d1, None, (None, torch.device("cuda"))), (d1, other, (other, d1)), (d0, side, (side, d0)),
+                            (d0, other, (other, d1)), (d0, Handle(), (Stream(0, 64), d0))):
+        assert spl._scratch(16, device, s) == (16,)
+        assert got.pop() == want, (device, s and s.cuda_stream)
