@@ -37,8 +37,9 @@ constexpr int kI8PieceRounds = kI8VBuf / 16 / kWave;
 constexpr int kI8XLdsMax = 32 * 1024;       // activations staged in LDS when M * 64 ceil(S/2) bytes fit
 constexpr int kI8OffsetLanes = kWave - 1;
 // Batches of more rows than one batch fragment go to the streaming kernel that stages activations through
-// LDS, where it can address them: per launch, this file's kernel / that one, q|k|v 13.9 / 14.4 us at 16
-// rows, 20.4 / 18.7 at 32, 55.1 / 32.2 at 127; gate|up 21.1 / 28.3, 34.6 / 30.9, 95.6 / 61.0.
+// LDS, where it can address them: per launch, this file's kernel / that one, q|k|v 16.8 / 12.4 us at 17
+// rows, 18.2 / 12.9 at 24, 20.2 / 13.8 at 32, 55.4 / 25.4 at 127; gate|up 27.7 / 20.2, 30.9 / 20.4, 34.7 /
+// 21.3, 97.6 / 46.2; down 13.4 / 12.1, 16.0 / 12.3, 17.6 / 12.9, 48.7 / 33.7.
 constexpr int64_t kI8WideMinM = 17;
 
 __device__ __forceinline__ i32x4 mfma_i8(u32x4 a, u32x4 b, i32x4 c) {

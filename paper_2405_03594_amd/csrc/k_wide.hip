@@ -124,10 +124,12 @@ __device__ __forceinline__ void wide_sum(typename WideAcc<T>::e* red, const type
   }
 }
 
-// The launch bound keeps the registers that the staged chunk needs (up to 142)
-// and lets LDS decide the workgroups per CU.
+// The launch bound keeps the registers that the staged chunk needs (up to 160)
+// and lets LDS decide the workgroups per CU; one row block of up to four
+// staged-row groups on 8 waves is held to 80, so that three share a CU (int8
+// at 32 rows took 82: q|k|v 23 us instead of 13.8, with the select below).
 template <class T, int R, int XG, int W, bool kGated>
-__global__ void __launch_bounds__(W * kWave, W == 16 ? 4 : W == 8 ? 2 : 3) k_sparse_wide(const WideGroupArg g) {
+__global__ void __launch_bounds__(W * kWave, W == 16 ? 4 : W == 8 ? (R == 1 && XG <= 4 ? 6 : 2) : 3) k_sparse_wide(const WideGroupArg g) {
   static_assert(!kGated || (R == 2 && !wide_q<T>()), "gated: a gate and an up block");
   constexpr bool kQ = wide_q<T>();
   constexpr int TC = kQ ? 4 : 2;                     // tiles per chunk; MFMA step j takes tile j (int8: 2j, 2j + 1)
@@ -326,7 +328,9 @@ __global__ void __launch_bounds__(W * kWave, W == 16 ? 4 : W == 8 ? 2 : 3) k_spa
           const uint32_t before = j ? ex[b] >> 16 : ex[b] & 0xffffu;
           u32x4 a;
           if constexpr (kQ) {
-            uint32_t p = before + ((fg >> 1) ? tile0[b][2 * j + 1] : tile0[b][2 * j]);
+            // (an arithmetic select: a conditional one is turned into a load from private memory)
+            const uint32_t t0 = tile0[b][2 * j], t1 = tile0[b][2 * j + 1];
+            uint32_t p = before + t0 + ((t1 - t0) & (0u - (uint32_t)(fg >> 1)));
 #pragma unroll
             for (int q = 0; q < 4; ++q) {            // a nibble's values: an aligned dword pair, realigned
               const uint32_t nib = __builtin_amdgcn_ubfe(wj[b][j], 4 * q, 4);
