@@ -409,54 +409,75 @@ hipError_t wide_launch(const WideGroupArg& g, hipStream_t s) {
 
 // Batch rows per workgroup: at most 64 (the activations of a chunk then take
 // 32 registers per lane and 8 KB of LDS per wave), the batch split evenly, in
-// the staged 8-row groups the kernel is built for.
-template <class T, int R, int W, bool kGated>
+// the staged 8-row groups the kernel is built for: kMin to kMax of them.
+int wide_splits(int M) { return (M + 63) / 64; }
+
+template <class T, int R, int W, bool kGated, int kMin, int kMax>
 hipError_t wide_rows(WideGroupArg& g, hipStream_t s) {
   for (int i = 0; i < g.count; ++i)
     g.first[i + 1] = g.first[i] + (int32_t)(kGated ? tile_blocks(g.t[i].N) : (tile_blocks(g.t[i].N) + R - 1) / R);
   if (kGated) g.first[g.count = 1] = (int32_t)tile_blocks(g.t[0].N);
-  const int splits = (g.M + 63) / 64;
+  const int splits = wide_splits(g.M);
   g.rows = (g.M + splits - 1) / splits;
-  if (g.rows <= 8) return wide_launch<T, R, 1, W, kGated>(g, s);
-  if (g.rows <= 16) return wide_launch<T, R, 2, W, kGated>(g, s);
-  if (g.rows <= 24) return wide_launch<T, R, 3, W, kGated>(g, s);
-  if (g.rows <= 32) return wide_launch<T, R, 4, W, kGated>(g, s);
-  if constexpr (W < 16) {
-    if (g.rows <= 48) return wide_launch<T, R, 6, W, kGated>(g, s);
-    return wide_launch<T, R, 8, W, kGated>(g, s);
-  } else {
-    return hipErrorNotSupported;                     // 16 waves: the picker keeps to 32 rows
+  if constexpr (kMin <= 1)
+    if (g.rows <= 8) return wide_launch<T, R, 1, W, kGated>(g, s);
+  if constexpr (kMin <= 2)
+    if (g.rows <= 16) return wide_launch<T, R, 2, W, kGated>(g, s);
+  if constexpr (kMin <= 4) {
+    if (g.rows <= 24) return wide_launch<T, R, 3, W, kGated>(g, s);
+    if (kMax <= 4 || g.rows <= 32) return wide_launch<T, R, 4, W, kGated>(g, s);
   }
+  if constexpr (kMax >= 8) {
+    if (kMin <= 6 && g.rows <= 48) return wide_launch<T, R, 6, W, kGated>(g, s);
+    return wide_launch<T, R, 8, W, kGated>(g, s);
+  }
+  return hipErrorNotSupported;                       // not reached: the pickers keep to kMin .. kMax
 }
 
-// Row blocks and waves per workgroup, from the row blocks per CU (4096 x 4096
-// launches have 1, q|k|v 3, gate|up 5.4) and the rows per workgroup.  Measured
-// on Llama-2-7B shapes, bf16 at 70% (us at 16 / 32 / 64 rows):
-//   below two blocks per CU: one block, 16 waves up to 32 rows (4096 x 4096:
-//     8.6 / 10.4; 8 waves 9.4 / 10.8), where 8 staged-row KB per wave still
-//     leave the LDS for them, 8 waves above (14.7; 4 waves 18.2);
-//   two to four: one block, 8 waves up to 48 rows (q|k|v 15.3 / 19.7; two
-//     blocks 17.9 / 20.6), two blocks on 4 waves above (29.9; 37.9);
-//   four or more: two blocks, 8 waves up to 40 rows (gate|up 23.9 / 30.1; one
-//     block 25.3 / 34.3), 4 waves above (40.5; 49.4), which leaves three
-//     workgroups per CU.
+// Row blocks (R) and waves (W) per workgroup, from the row blocks per CU
+// (4096 x 4096 launches have 1, q|k|v 3, gate|up 5.4) and the rows per
+// workgroup.  One workgroup of 16 waves fits a CU, so that form is for up to
+// one block per CU: 288 blocks (3 x 1536 x 1536) are two rounds of it.
+// Measured, us per launch at 70%, bf16 unless said:
+//   up to 32 rows, one block per CU: R 1, W 16 (4096 x 4096 at 16 rows 8.3; W
+//     8 9.9); below 3.5 per CU: R 1, W 8 (3 x 1536 x 1536 at 16 rows 7.0; W 16
+//     8.8); above: R 2, W 8, whose activations serve two blocks (gate|up at 32
+//     rows 31.5; R 1 36.6; 3 x 5120 x 5120 at 16 rows 22.1; 26.1), except up to
+//     8 rows, whose activations are few: R 1, W 8 (2 x 9216 x 3072 at 8 rows
+//     16.8; R 2 20.2; 2 x 13824 x 5120 33.4; 38.0);
+//   more rows, R 1 workgroups (blocks times the splits of the batch) up to one
+//     per CU: R 1, W 8 (4096 x 4096 at 64 rows 13.9; W 4 18.2); up to one block
+//     per CU in two splits: R 1, W 8 up to 48 rows each, else R 2, W 8
+//     (4096 x 11008 at 128 rows 38.9; R 1 54.4); below 3.5 per CU: R 1, W 4
+//     (q|k|v at 64 rows int8 19.6; W 8 25.9); above: R 2, W 4, three workgroups
+//     per CU (gate|up at 65 rows 62; R 2 W 8 85; at 33 rows 34.8; 44.9).
 template <class T>
 hipError_t wide_pick(WideGroupArg& g, hipStream_t s) {
   int64_t blocks = 0;
   for (int i = 0; i < g.count; ++i) blocks += tile_blocks(g.t[i].N);
-  const int64_t cus = device_cus();
-  const int rows = (g.M + (g.M + 63) / 64 - 1) / ((g.M + 63) / 64);
-  if (blocks < 2 * cus) return rows <= 32 ? wide_rows<T, 1, 16, false>(g, s) : wide_rows<T, 1, 8, false>(g, s);
-  if (blocks < 4 * cus) return rows <= 48 ? wide_rows<T, 1, 8, false>(g, s) : wide_rows<T, 2, 4, false>(g, s);
-  return rows <= 40 ? wide_rows<T, 2, 8, false>(g, s) : wide_rows<T, 2, 4, false>(g, s);
+  const int64_t cus = device_cus(), splits = wide_splits(g.M);
+  const int64_t rows = (g.M + splits - 1) / splits;
+  if (rows <= 32) {
+    if (blocks <= cus) return wide_rows<T, 1, 16, false, 1, 4>(g, s);
+    if (2 * blocks < 7 * cus || (rows <= 8 && blocks < 16 * cus)) return wide_rows<T, 1, 8, false, 1, 8>(g, s);
+    return wide_rows<T, 2, 8, false, 1, 8>(g, s);
+  }
+  if (blocks * splits <= cus || (blocks <= cus && rows <= 48)) return wide_rows<T, 1, 8, false, 1, 8>(g, s);
+  if (blocks <= cus) return wide_rows<T, 2, 8, false, 1, 8>(g, s);
+  return 2 * blocks * splits < 7 * cus ? wide_rows<T, 1, 4, false, 6, 8>(g, s) : wide_rows<T, 2, 4, false, 6, 8>(g, s);
 }
 
+// The gated half, by its pairs of row blocks: up to 32 rows W 16 up to one pair
+// per CU, W 8 above (2 x 5632 x 2048, 352 pairs, at 8 rows 10.3; W 16 12.8);
+// more rows: W 8 up to one workgroup per CU, W 4 above (gate|up at 33 rows
+// 34.6; W 8 44.0; at 65 62.0; 83.8).
 template <class T>
 hipError_t wide_pick_gated(WideGroupArg& g, hipStream_t s) {
-  const int64_t pairs = tile_blocks(g.t[0].N);
-  const int rows = (g.M + (g.M + 63) / 64 - 1) / ((g.M + 63) / 64);
-  if (pairs < 2 * (int64_t)device_cus() && rows <= 32) return wide_rows<T, 2, 16, true>(g, s);
-  return rows <= 40 || pairs < 2 * (int64_t)device_cus() ? wide_rows<T, 2, 8, true>(g, s) : wide_rows<T, 2, 4, true>(g, s);
+  const int64_t pairs = tile_blocks(g.t[0].N), cus = device_cus(), splits = wide_splits(g.M);
+  const int64_t rows = (g.M + splits - 1) / splits;
+  if (rows <= 32)
+    return pairs <= cus ? wide_rows<T, 2, 16, true, 1, 4>(g, s) : wide_rows<T, 2, 8, true, 1, 8>(g, s);
+  return pairs * splits <= cus ? wide_rows<T, 2, 8, true, 1, 8>(g, s) : wide_rows<T, 2, 4, true, 6, 8>(g, s);
 }
 
 WideTaskArg wide_task(const void* X, const spl_matrix& W, void* Y) {

@@ -2,9 +2,9 @@
 2..128 rows, the gated half up to 112, int8 from 17 rows) on the GPU vs the
 oracle: fp16/bf16 within the parity tolerance, int8 bit for bit.
 
-The shapes put its edges in play: grids below two, of two to four and of four
-and more row blocks per CU (one or two row blocks and 4, 8 or 16 waves per
-workgroup; an odd number of row blocks for the pairs), every staged-row group
+The shapes put its edges in play: grids of up to one, below and above 3.5 row
+blocks per CU (one or two row blocks and 4, 8 or 16 waves per workgroup; an odd
+number of row blocks for the pairs), every staged-row group
 count and both sides of each, a batch split over two workgroups, a last chunk
 of one tile, columns past K, full tiles off a 16-byte boundary (129 value
 pieces), an all-pruned matrix, and ranges longer than one offsets window."""
@@ -43,10 +43,12 @@ def _packed(spl, W, mask, dtype):
     return spl.pack_sparse(to_dev(W, dtype), torch.from_numpy(mask).cuda())
 
 
-# 8192 < N: 513 row blocks (two to four per CU of 256); 16384 < N: 1025 (four and more, an odd number)
+# 8192 < N: 513 row blocks (two per CU of 256); 16384 < N: 1025 (four, an odd number); 2100: 132, more than one
+# workgroup per CU in two splits; 4800: 300, more than one per CU, below 3.5 in two splits
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("N,K,s", [(1, 8, 0.5), (33, 96, 0.7), (100, 1000, 0.5), (48, 160, -1.0), (17, 264, 1.0),
-                                   (40, 2088, 0.7), (8200, 72, 0.6), (16390, 136, 0.6), (16390, 64, -1.0)])
+                                   (40, 2088, 0.7), (8200, 72, 0.6), (16390, 136, 0.6), (16390, 64, -1.0),
+                                   (2100, 200, 0.6), (4800, 136, 0.6)])
 def test_wide_linear(orc, spl, dtype, N, K, s):
     W, mask = _weight(900 + N + K, N, K, dtype, s)
     X = synth.activations(901 + K, max(BATCHES), K, dtype)
@@ -89,18 +91,20 @@ def test_wide_group(orc, spl, M):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("N,K,s", [(40, 72, 0.7), (100, 1000, 0.5), (8200, 96, 0.6)])
+@pytest.mark.parametrize("N,K,s", [(40, 72, 0.7), (100, 1000, 0.5), (8200, 96, 0.6),
+                                   (2100, 1096, 0.6), (4800, 1096, 0.6)])
 def test_wide_gated(orc, spl, dtype, N, K, s):
     (Wg, mg), (Wu, mu) = (_weight(600 + i + N, N, K, dtype, s) for i in range(2))
     X = synth.activations(602 + K, 112, K, dtype)
     ref = orc.silu_mul_f64(X, orc.pack(Wg, dtype, mg), orc.pack(Wu, dtype, mu))
     g, u, Xd = _packed(spl, Wg, mg, dtype), _packed(spl, Wu, mu, dtype), to_dev(X, dtype)
-    for M in (1, 8, 17, 32, 33, 41, 64, 65, 112):
+    for M in (1, 2, 8, 9, 16, 17, 32, 33, 41, 64, 65, 112):
         Y = spl.sparse_linear_silu_mul(Xd[:M].contiguous(), g, u)
         assert_close(from_dev_f64(Y), ref[:M], f"{dtype} N={N} K={K} M={M}")
 
 
-@pytest.mark.parametrize("N,K,s", [(33, 112, 0.7), (64, 2064, 0.5), (48, 160, 0.0), (8200, 80, 0.6), (16390, 144, 0.6)])
+@pytest.mark.parametrize("N,K,s", [(33, 112, 0.7), (64, 2064, 0.5), (48, 160, 0.0), (8200, 80, 0.6), (16390, 144, 0.6),
+                                   (2100, 144, 0.6), (4800, 80, 0.6)])
 def test_wide_int8(orc, spl, N, K, s):
     import torch
 
