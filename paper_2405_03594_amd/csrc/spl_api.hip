@@ -259,7 +259,7 @@ spl_status spl_sparse_linear_group(const spl_sparse_task* tasks, int32_t count, 
   if (blocks >= kMaxDim) return SPL_ERR_OVERFLOW;
   if (M == 0) return SPL_OK;
   (void)hipGetLastError();
-  if (wide) return launched(spl::launch_sparse_wide(tasks, count, M, stream));
+  if (wide && !spl::few_rows_decode(M, blocks)) return launched(spl::launch_sparse_wide(tasks, count, M, stream));
   if (algo == SPL_ALGO_AUTO && M <= kStreamMaxM && resolved == SPL_ALGO_DECODE)
     return launched(spl::launch_sparse_row(tasks, count, stream));
   if (resolved == SPL_ALGO_DECODE) return launched(spl::launch_sparse_decode(tasks, count, M, stream));
