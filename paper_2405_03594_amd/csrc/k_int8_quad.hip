@@ -67,9 +67,11 @@ __device__ __forceinline__ uint32_t shift64(uint32_t hi, uint32_t lo, uint32_t b
   return (uint32_t)((((uint64_t)hi << 32) | lo) >> bits);
 }
 
-// One task: its arguments are loaded without a search for it first.
+// One task: its arguments are loaded without a search for it first.  The
+// launch bound leaves three 8-wave workgroups per CU (81 registers otherwise,
+// two: 11008 x 4096 at one row 12.2 us instead of 8.9).
 template <int W, bool kGroup>
-__global__ void __launch_bounds__(W * kWave) k_int8_quad(const I8QuadGroupArg g) {
+__global__ void __launch_bounds__(W * kWave, W == 8 ? 6 : 1) k_int8_quad(const I8QuadGroupArg g) {
   __shared__ i32x4 part[W][64];
   __shared__ uint32_t sel4[16];
   // a quad's values from a 16-byte boundary (full tiles: kPieces pieces and one more; a lane reads at most 16 bytes
@@ -256,11 +258,14 @@ hipError_t launch_int8_quad(const spl_int8_task* tasks, int count, int64_t M, hi
   g.M = (int32_t)M;
   for (int i = 0; i < count; ++i)
     i8q_add(g, tasks[i].Xq, tasks[i].x_scales, *tasks[i].Wq, tasks[i].w_scales, tasks[i].Y, tasks[i].acc_out);
-  // Waves per row block (us per step of four layers, hidden 4096, ffn 11008, at 1 / 16 rows).  Below two blocks per
-  // CU (o, down) 16: 8 there 241 / 282 instead of 224 / 267.  From four per CU (gate|up, 5.4) 4, whose longer ranges
-  // hide more of a wave's start: 8 there 234 / 275.  Between (q|k|v, 3) 8: 4 there 229 / 265.
+  // Waves per row block, us per launch at 70%, 8 rows.  Up to one block per CU, where each wave has a quad, 16: 4096 x
+  // 4096 6.0, with 8 6.8; 4096 x 11008 9.8, 12.4; but 2 x 2048 x 768 (6 quads) 4.5, 4.2.  Above, 16 waves are one
+  // workgroup per CU, so two rounds below two blocks per CU: 3 x 1536 x 1536 (288 blocks) 7.4, with 8 5.8.  From four
+  // per CU 4, whose longer ranges hide more of a wave's start: gate|up (5.4) 15.1, with 8 19.4; q|k|v (3) 11.5, 9.9.
+  int64_t kmax = 0;
+  for (int i = 0; i < count; ++i) kmax = tasks[i].Wq->cols > kmax ? tasks[i].Wq->cols : kmax;
   const int64_t blocks = g.first[g.count], cus = device_cus();
-  if (blocks < 2 * cus) return i8q_launch<16>(g, s);
+  if (blocks <= cus && kmax >= 16 * 128) return i8q_launch<16>(g, s);
   return blocks < 4 * cus ? i8q_launch<8>(g, s) : i8q_launch<4>(g, s);
 }
 

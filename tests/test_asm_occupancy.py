@@ -40,3 +40,6 @@ def test_no_private_memory(source, tmp_path_factory):
     if source == "k_wide":                             # one row block, up to four staged-row groups, 8 waves
         eight = {k: v for k, v in kernels.items() if re.search(r"k_sparse_wideI.*Li1ELi[1-4]ELi8ELb0E", k)}
         assert len(eight) == 12 and all(v[1] >= 6 for v in eight.values()), eight
+    if source == "k_int8_quad":
+        eight = {k: v for k, v in kernels.items() if "Li8E" in k}
+        assert len(eight) == 2 and all(v[1] >= 6 for v in eight.values()), eight

@@ -2,9 +2,9 @@
 up to 16 rows) on the GPU, bit for bit against the oracle.
 
 The shapes put its edges in play: last quads of one to four tiles, half tiles
-(K % 32 == 16), waves with no, one, two and several quads, grids on both sides
-of two row blocks per CU (16 or 8 waves), full and empty tiles, and batches on
-both sides of the turned activations."""
+(K % 32 == 16), waves with no, one, two and several quads, grids of up to one
+row block per CU (16 waves, 8 where K has fewer than 16 quads), below and from
+four per CU (8 and 4 waves), and full and empty tiles."""
 import numpy as np
 import pytest
 
@@ -32,7 +32,8 @@ def _bits(Y):
 
 @pytest.mark.parametrize("N,K,s", [(5, 32, 0.5), (33, 80, 0.6), (17, 112, 0.0), (40, 128, 0.7), (20, 144, 0.7),
                                    (100, 2048, 0.5), (31, 4112, 0.7), (16, 6208, 0.3), (48, 13824, 0.7),
-                                   (8208, 208, 0.7), (8300, 2080, 0.6), (24, 1024, 1.0)])
+                                   (8208, 208, 0.7), (8300, 2080, 0.6), (24, 1024, 1.0), (4112, 2064, 0.6),
+                                   (16390, 144, 0.6), (16390, 2064, 0.6)])
 def test_int8_quad(orc, spl, N, K, s):
     import torch
 
@@ -66,6 +67,22 @@ def test_int8_quad_group(orc, spl, M):
                      spl.pack_sparse(to_dev(Wq, "i8"), torch.from_numpy(mask).cuda()), torch.from_numpy(sw).cuda()))
     outs = spl.sparse_linear_int8_group(*[list(a) for a in zip(*args)])
     for i, (y, ref) in enumerate(zip(outs, refs)):
+        _assert_equal(_bits(y), ref, f"task {i} M={M}")
+
+
+@pytest.mark.parametrize("M", (1, 8, 16))
+def test_int8_quad_large_group(orc, spl, M):
+    """More than four row blocks per CU in one launch (4 waves), both tasks with a last partial block."""
+    import torch
+
+    args, refs = [], []
+    for i, (N, K, s) in enumerate([(9000, 144, 0.6), (8200, 272, 0.5)]):
+        Wq, mask, sw = synth.int8_weight(970 + i, N, K, s)
+        Xq, sx = synth.int8_activations(980 + i, M, K)
+        refs.append(orc.linear_i8(Xq, sx, orc.pack(Wq, "i8", mask), sw)[1])
+        args.append((to_dev(Xq, "i8"), torch.from_numpy(sx).cuda(),
+                     spl.pack_sparse(to_dev(Wq, "i8"), torch.from_numpy(mask).cuda()), torch.from_numpy(sw).cuda()))
+    for i, (y, ref) in enumerate(zip(spl.sparse_linear_int8_group(*[list(a) for a in zip(*args)]), refs)):
         _assert_equal(_bits(y), ref, f"task {i} M={M}")
 
 
