@@ -206,12 +206,11 @@ hipError_t launch_sparse_int4(const int8_t* Xq, const float* sx, int64_t M, cons
                               void* Y, int32_t* acc_out, hipStream_t s) {
   // the kernel addresses X, a row block's words and its tile offsets with 32-bit buffer offsets
   if (M * W4.cols >= (int64_t)1 << 31 || tile_steps(W4.cols) >= (int64_t)1 << 25) return hipErrorNotSupported;
-  // Four tiles per scan, where 16 x the sums of a wave's columns stay in 32 bits and there are more quads than waves
-  // (16 on grids below two row blocks per CU, else 8).  Launches in us, this kernel / that one, at 1 / 5 / 16 rows:
-  // 16 waves (4096 rows, 70%), 2048 columns 5.1 5.1 5.3 / 5.0 5.5 5.5, 3072 6.3 6.2 6.5 / 4.9 5.2 5.3; 8 waves (11008
-  // rows), 768 columns 5.3 5.4 5.7 / 5.3 5.6 5.7, 1536 7.2 7.2 7.7 / 5.7 5.7 5.9.
-  const int64_t waves = tile_blocks(W4.rows) < 2 * (int64_t)device_cus() ? 16 : 8;
-  if (W4.cols > 128 * waves && W4.cols <= kInt4QuadMaxK) return launch_int4_quad(Xq, sx, M, W4, sw, Y, acc_out, s);
+  // Four tiles per scan, where 16 x the sums of a wave's columns stay in 32 bits and there are more quads than waves.
+  // Launches in us (70%, cold weights), this kernel / that one, at 1 / 5 / 16 rows: 16 waves, 2048 x 2048 4.8 4.9 5.1
+  // / 4.5 5.0 5.1, 4096 x 4096 7.0 7.1 7.4 / 5.3 5.5 5.8; 8 waves, 5632 x 2048 6.9 7.0 7.3 / 5.1 5.4 5.5, 11008 x 4096
+  // 12.6 12.7 13.4 / 8.6 9.0 9.2.
+  if (W4.cols > 128 * int4_quad_waves(W4.rows) && W4.cols <= kInt4QuadMaxK) return launch_int4_quad(Xq, sx, M, W4, sw, Y, acc_out, s);
   I4Args g{Xq, sx, W4.bitmask, static_cast<const uint8_t*>(W4.values), W4.tile_offsets, sw,
            static_cast<uint16_t*>(Y), acc_out, W4.rows, W4.cols, (int32_t)M};
   const int64_t blocks = tile_blocks(W4.rows);

@@ -13,7 +13,7 @@
 //     first values of all eight operands of the quad's rows;
 //   * a lane's (at most 16) codes of a group are one 12-byte load, shifted into
 //     place and then by the counts of its 4-column nibbles in registers (staged
-//     in LDS as in k_int8_quad.hip, four layers' step took 245 us instead of 231);
+//     in LDS as in k_int8_quad.hip, the step took 6% longer);
 //   * a code is used in the upper half of its byte, where it is 16 x the code
 //     with no sign extension: for four columns whose codes start at bit 0 of t,
 //     the bytes of {t << 4, t} hold them in their upper halves, so one
@@ -23,15 +23,18 @@
 //   * a load of the MFMA activation operand touches 16 rows in 16 consecutive
 //     lanes, one cache access per lane (64 cycles); from kTurnMinM rows on a
 //     wave loads 128-byte runs, 8 lanes per row, and turns them in its own LDS,
-//     written one quad ahead (us per step of four layers, direct / turned: 4
-//     rows 240 / 241, 8 rows 258 / 247, 16 rows 298 / 254);
+//     written one quad ahead (us per launch, direct / turned, at 1, 4, 8 and 16
+//     rows: 4096 x 4096 5.3 / 5.5, 5.6 / 5.5, 5.8 / 5.6, 6.5 / 5.8; 11008 x 4096
+//     8.6 / 8.9, 9.1 / 8.9, 9.6 / 9.0, 11.2 / 9.2);
 //   * words, offsets, codes and activations are buffer loads that end at the
 //     wave's range, so nothing is clamped; words and offsets are two quads
-//     ahead, codes and activations one, and no load is waited for in the quad
-//     that issues it.
+//     ahead, codes and activations one.  Direct, no load is waited for in the
+//     quad that issues it; turned, the next quad's activations are, at its end,
+//     where they go to LDS.
 //
-// Four layers' step (hidden 4096, ffn 11008, 70%), k_int4.hip's kernel / this
-// one: 306 / 218 us at one row, 326 / 244 at 16.
+// Launches at 70% and cold weights, k_int4.hip's kernel / this one, at 1 and 16
+// rows: 4096 x 4096 7.0 / 5.3, 7.4 / 5.8 us; 4096 x 11008 12.7 / 8.4, 13.5 / 9.4;
+// 11008 x 4096 12.6 / 8.7, 13.4 / 9.2.
 #include "spl_common.h"
 
 namespace spl {
@@ -263,9 +266,7 @@ hipError_t launch_int4_quad(const int8_t* Xq, const float* sx, int64_t M, const 
   const I4QuadArg g{Xq, sx, W4.bitmask, static_cast<const uint8_t*>(W4.values), W4.tile_offsets, sw,
                     static_cast<uint16_t*>(Y), acc_out, W4.rows, W4.cols,
                     (uint32_t)spl_values_bytes(W4.dtype, W4.nnz), (int32_t)M};
-  // below two row blocks per CU their waves split the columns twice as far (hidden x hidden, ffn columns: the step of
-  // four layers 230 / 241 us on 16 / 8 waves)
-  return tile_blocks(W4.rows) < 2 * (int64_t)device_cus() ? i4_launch<16>(g, s) : i4_launch<8>(g, s);
+  return int4_quad_waves(W4.rows) == 16 ? i4_launch<16>(g, s) : i4_launch<8>(g, s);
 }
 
 }  // namespace spl

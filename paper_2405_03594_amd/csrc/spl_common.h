@@ -303,6 +303,10 @@ hipError_t launch_sparse_int4(const int8_t* Xq, const float* sx, int64_t M, cons
 // The same by quads of tiles: M <= 16, M K < 2^31, K <= kInt4QuadMaxK (its sums are 16 x the codes': a wave of at
 // least 8 multiplies (2^20 / 8 + 128) columns, half of them per accumulator, 2^14 at most each).
 constexpr int64_t kInt4QuadMaxK = (int64_t)1 << 20;
+// Its waves per row block.  16 are one workgroup per CU, so they are for up to one block per CU; above, one round of
+// 8 takes less than two of 16.  Launches at 8 rows, 16 / 8 waves: 4096 x 4096 (1 per CU) 5.6 / 5.8 us, 4096 x 11008
+// 8.7 / 10.2, 5632 x 2048 (1.4) 8.9 / 5.3, 11008 x 4096 (2.7) 13.3 / 9.0.
+inline int int4_quad_waves(int64_t rows) { return tile_blocks(rows) <= (int64_t)device_cus() ? 16 : 8; }
 hipError_t launch_int4_quad(const int8_t* Xq, const float* sx, int64_t M, const spl_matrix& W4, const float* sw,
                             void* Y, int32_t* acc_out, hipStream_t s);
 // int8 groups of up to 16 rows whose activations and words it can address.

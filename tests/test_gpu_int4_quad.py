@@ -3,7 +3,7 @@ to 2^20) on the GPU, bit for bit against the int8 oracle on the same codes.
 
 The shapes put its edges in play: last quads of one to four tiles, half tiles
 (K % 32 == 16), waves with no, one, two and several quads, grids on both sides
-of two row blocks per CU (16 or 8 waves), full and empty tiles, batches of 1 to
+of one row block per CU (16 or 8 waves), full and empty tiles, batches of 1 to
 16 rows, and the largest sums on both sides of the 2^20 columns from where the
 other kernel runs."""
 import numpy as np
@@ -38,7 +38,8 @@ def _run(spl, Xq, sx, W4, sw, N):
 
 @pytest.mark.parametrize("N,K,s", [(5, 32, 0.5), (33, 80, 0.6), (17, 112, 0.0), (40, 128, 0.7), (20, 144, 0.7),
                                    (100, 2048, 0.5), (31, 4112, 0.7), (16, 6208, 0.3), (48, 13824, 0.7),
-                                   (8208, 208, 0.7), (8300, 2080, 0.6), (24, 1024, 1.0)])
+                                   (8208, 208, 0.7), (8300, 2080, 0.6), (24, 1024, 1.0), (4112, 1040, 0.6),
+                                   (4112, 3088, 0.6), (4090, 3088, 0.6)])
 def test_int4_quad(orc, spl, N, K, s):
     Wq, mask, sw = synth.int4_weight_full_range(930 + N, N, K, s)
     W4 = _pack4(spl, Wq, mask)
