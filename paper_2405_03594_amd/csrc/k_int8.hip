@@ -41,6 +41,13 @@ constexpr int kI8OffsetLanes = kWave - 1;
 // rows, 18.2 / 12.9 at 24, 20.2 / 13.8 at 32, 55.4 / 25.4 at 127; gate|up 27.7 / 20.2, 30.9 / 20.4, 34.7 /
 // 21.3, 97.6 / 46.2; down 13.4 / 12.1, 16.0 / 12.3, 17.6 / 12.9, 48.7 / 33.7.
 constexpr int64_t kI8WideMinM = 17;
+// On up to one row block per CU, where the four-tile kernel waits for its activations most, from 12 rows, or 16 past
+// 4096 columns: its launches / the streaming ones at 12, 14 and 16 rows 3072 x 3072 5.8 / 5.4, 5.9 / 5.4, 6.1 / 5.4
+// us, 4096 x 4096 6.2 / 6.2, 6.4 / 6.2, 6.6 / 6.2, 4096 x 11008 10.1 / 10.6, 10.4 / 10.7, 10.9 / 10.8; q|k|v, 3
+// blocks per CU, 10.9 / 11.2 at 12.
+bool i8_wide_small(int64_t M, int64_t blocks, int64_t kmax) {
+  return M >= (kmax <= 4096 ? 12 : 16) && blocks <= device_cus();
+}
 
 __device__ __forceinline__ i32x4 mfma_i8(u32x4 a, u32x4 b, i32x4 c) {
   return __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x4, b), c, 0, 0,
@@ -521,11 +528,17 @@ hipError_t launch_sparse_int8(const spl_int8_task* tasks, int count, int64_t M, 
     }
     return hipSuccess;
   }
-  bool wide = M >= kI8WideMinM;
+  int64_t blocks = 0, kmax = 0;
+  for (int i = 0; i < count; ++i) {
+    blocks += tile_blocks(tasks[i].Wq->rows);
+    kmax = tasks[i].Wq->cols > kmax ? tasks[i].Wq->cols : kmax;
+  }
+  bool wide = M >= kI8WideMinM || i8_wide_small(M, blocks, kmax);
   for (int i = 0; i < count; ++i) wide = wide && sparse_wide_fits(M, tasks[i].Wq->cols, 1);
   if (wide) return launch_int8_wide(tasks, count, M, s);
-  // Up to one batch fragment four tiles per scan, where 32 bits address the activations: a step of four layers this
-  // file's kernel / that one 236 / 221 us at 1 row, 288 / 229 at 8, 285 / 264 at 16.
+  // Up to one batch fragment four tiles per scan, where 32 bits address the activations: launches of this file's
+  // kernel / that one at 1 and 8 rows 4096 x 4096 6.6 / 5.7, 7.0 / 6.0 us, q|k|v 11.0 / 9.8, 14.3 / 9.9, gate|up
+  // 16.7 / 14.8, 23.4 / 15.1.
   bool quad = M <= 16;
   for (int i = 0; i < count; ++i) quad = quad && int8_quad_fits(M, tasks[i].Wq->cols);
   if (quad) return launch_int8_quad(tasks, count, M, s);
@@ -533,17 +546,14 @@ hipError_t launch_sparse_int8(const spl_int8_task* tasks, int count, int64_t M, 
   g.count = count;
   g.M = (int32_t)M;
   g.first[0] = 0;
-  int64_t kmax = 0;
   for (int i = 0; i < count; ++i) {
     const spl_matrix& W = *tasks[i].Wq;
     g.t[i] = I8TaskArg{tasks[i].Xq, tasks[i].x_scales, W.bitmask, static_cast<const uint8_t*>(W.values),
                        W.tile_offsets, W.rows, W.cols, tasks[i].w_scales, static_cast<uint16_t*>(tasks[i].Y),
                        tasks[i].acc_out};
     g.first[i + 1] = g.first[i] + (int32_t)tile_blocks(W.rows);
-    kmax = W.cols > kmax ? W.cols : kmax;
   }
-  const int64_t blocks = (int64_t)g.first[count] * ((M + 63) / 64);
-  return i8_small_grid(blocks) ? sparse_int8_w<16>(g, kmax, s) : sparse_int8_w<8>(g, kmax, s);
+  return i8_small_grid(blocks * ((M + 63) / 64)) ? sparse_int8_w<16>(g, kmax, s) : sparse_int8_w<8>(g, kmax, s);
 }
 
 hipError_t launch_dense_int8(const spl_dense_int8_task* tasks, int count, int64_t M, hipStream_t s) {

@@ -1,5 +1,5 @@
 """The streaming kernel of several batch fragments (k_wide.hip: AUTO batches of
-2..128 rows, the gated half up to 112, int8 from 17 rows) on the GPU vs the
+2..128 rows, the gated half up to 112, int8 from 17 rows, from 12 on small grids) on the GPU vs the
 oracle: fp16/bf16 within the parity tolerance, int8 bit for bit.
 
 The shapes put its edges in play: grids of up to one, below and above 3.5 row
@@ -117,7 +117,7 @@ def test_wide_int8(orc, spl, N, K, s):
     p = orc.pack(Wq, "i8", mask)
     Wc = _packed(spl, Wq, mask, "i8")
     Xd, sxd, swd = to_dev(Xq, "i8"), torch.from_numpy(sx).cuda(), torch.from_numpy(sw).cuda()
-    for M in (17, 24, 32, 33, 48, 64, 65, 127):
+    for M in (11, 12, 15, 16, 17, 24, 32, 33, 48, 64, 65, 127):
         acc_ref, y_ref = orc.linear_i8(Xq[:M], sx[:M], p, sw)
         acc = torch.empty((M, N), dtype=torch.int32, device="cuda")
         Y = spl.sparse_linear_int8(Xd[:M].contiguous(), sxd[:M].contiguous(), Wc, swd, acc_out=acc)
