@@ -92,9 +92,12 @@ def test_wide_group(orc, spl, M):
         assert (o[M] == 7.0).all(), f"task {i}: written past its output"
 
 
+# 1024 and 1032 columns: both sides of where 9 to 16 rows take the decode kernel; 7160 .. 8192 rows: of where more than
+# 64 rows are expanded in place
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("N,K,s", [(40, 72, 0.7), (100, 1000, 0.5), (8200, 96, 0.6),
-                                   (2100, 1096, 0.6), (4800, 1096, 0.6)])
+                                   (2100, 1096, 0.6), (4800, 1096, 0.6), (33, 1024, 0.7), (33, 1032, 0.7),
+                                   (7160, 72, 0.6), (7170, 72, 0.6), (8192, 72, 0.6)])
 def test_wide_gated(orc, spl, dtype, N, K, s):
     (Wg, mg), (Wu, mu) = (_weight(600 + i + N, N, K, dtype, s) for i in range(2))
     X = synth.activations(602 + K, 112, K, dtype)
