@@ -465,16 +465,17 @@ spl_status spl_dense_linear_group(const spl_dense_task* tasks, int32_t count, in
  * one launch.  The results are those of the plain call up to the order of the
  * fp32 sums (int8: identical).
  *   *_scratch_bytes  device bytes the call can use; 0 where it would use none
- *                    (small batches, or sizes past the decoded product's
- *                    32-bit addressing); -1 for arguments the call rejects.
+ *                    (small batches, sizes where expanding in place is the
+ *                    faster way, or past the decoded product's 32-bit
+ *                    addressing); -1 for arguments the call rejects.
  *   scratch          256-byte aligned, caller-owned, overwritten; NULL, or
  *                    scratch_bytes below what the size function returns, gives
  *                    the plain call.  One buffer can serve calls in turn on
  *                    one stream.
  * spl_sparse_input_grad_scratch computes spl_sparse_input_grad through W's
- * decoded transpose (rows % 8 == 0); its size function returns 0 otherwise and
- * the call is then SPL_ERR_UNSUPPORTED without scratch (it has no other
- * workspace). */
+ * decoded transpose (rows % 8 == 0).  Without usable scratch, or where its size
+ * function returns 0, it reads W's packed tiles where spl_sparse_input_grad needs
+ * no workspace, and is SPL_ERR_UNSUPPORTED elsewhere. */
 int64_t spl_sparse_linear_group_scratch_bytes(const spl_sparse_task* tasks, int32_t count, int64_t M);
 spl_status spl_sparse_linear_group_scratch(const spl_sparse_task* tasks, int32_t count, int64_t M, void* scratch,
                                            int64_t scratch_bytes, hipStream_t stream);

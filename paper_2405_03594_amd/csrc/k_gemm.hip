@@ -531,7 +531,7 @@ hipError_t fg_launch(FgGroupArg& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Workgroup tile of a launch: the one whose rounds over the chip cost least.
+// Workgroup tile of a launch and its cost: the one whose rounds over the chip cost least.
 // Costs are us per 64 stages measured on 4096-column launches (bf16): one
 // workgroup of 128 x 256 per CU 60; of 128 x 128, two per CU, 32 for one and
 // 62 for both; of 64 x 128, four per CU, 24, 42, 60 and 78.  So gate|up at
@@ -539,23 +539,81 @@ hipError_t fg_launch(FgGroupArg& g, hipStream_t s) {
 // 128 x 256), q|k|v there 128 x 256 (179; 185), q at 512 tokens 64 x 128
 // (24.5; 31 and 50 with the larger ones).
 enum { kFgL, kFgM, kFgS };
-int fg_tile(const FgGroupArg& g, bool gated) {
+struct FgCost {
+  int tile;
+  int64_t us;                    // per 64 stages
+};
+FgCost fg_cost(const int64_t* N, int count, int64_t M) {   // rows of each task (gated: of both matrices)
   const int64_t cus = device_cus();
   auto tiles = [&](int rn, int bm) {
     int64_t n = 0;
-    for (int i = 0; i < g.count; ++i) n += (g.t[i].N * (gated ? 2 : 1) + rn - 1) / rn;
-    return n * ((g.M + bm - 1) / bm);
+    for (int i = 0; i < count; ++i) n += (N[i] + rn - 1) / rn;
+    return n * ((M + bm - 1) / bm);
   };
   const int64_t l = tiles(128, 256), m = tiles(128, 128), q = tiles(64, 128);
   const int64_t cl = (l + cus - 1) / cus * 60;
   const int64_t mr = m % (2 * cus), cm = m / (2 * cus) * 62 + (mr == 0 ? 0 : mr <= cus ? 32 : 62);
   const int64_t qr = (q % (4 * cus) + cus - 1) / cus, cq = q / (4 * cus) * 78 + (qr == 0 ? 0 : 6 + 18 * qr);
-  return cl <= cm && cl <= cq ? kFgL : cm <= cq ? kFgM : kFgS;
+  return cl <= cm && cl <= cq ? FgCost{kFgL, cl} : cm <= cq ? FgCost{kFgM, cm} : FgCost{kFgS, cq};
+}
+
+// Us of the kernel that expands N x K in place for M rows of 16-bit payloads
+// (gated: N rows of both matrices), from its tiles (k_prefill.hip): 128 x 256,
+// one per CU, rounds of 1.38 us a stage of 64 columns; 64 x 128, up to one per
+// CU 0.66 (K split), else 0.25 and 0.39 for each tile of a CU.
+double fg_inplace_us(int64_t N, int64_t K, int64_t M) {
+  const int64_t cus = device_cus(), st = (K + 63) / 64;
+  const int64_t large = ((N + 127) / 128) * ((M + 255) / 256), small = ((N + 63) / 64) * ((M + 127) / 128);
+  if (large >= cus) return (double)((large + cus - 1) / cus) * (4 + 1.38 * st);
+  if (small <= cus) return 4 + 0.66 * st;
+  return 4 + (0.25 + 0.39 * ((small + cus - 1) / cus)) * st;
+}
+
+// Us of decoding matrices into `bytes` of fragments at 3.3 TB/s and of their
+// product: 7 us (gated 9) beside fg_cost, with 8 stages more for the product's
+// ends, or reading the fragments at 2.8 TB/s.
+double fg_decoded_us(const int64_t* N, int count, int64_t K, int64_t M, int64_t bytes, bool gated) {
+  const double product = (double)fg_cost(N, count, M).us * ((K + 63) / 64 + 8) / 72, read = bytes / 2.8e6;
+  return (gated ? 9 : 7) + bytes / 3.3e6 + (product > read ? product : read);
+}
+
+// Whether a call gains by decoding its matrices into scratch first.  int8
+// always does (4096 x 4096 at 129 rows 32 us in place, 27 decoded; q|k|v 93,
+// 34), but for one small matrix, where issuing the call from eager code costs
+// more than the kernel (18 us with scratch, 12 without; 1024 x 1024 at 129 rows
+// takes 16 us in place).  16-bit payloads by the estimates above; in place has to
+// come to the 16 us that issuing a call with scratch takes.  Over 1022 launches
+// on 31 sets of widths (K 512 to 11008, 113 to 2048 rows) they pick the slower
+// way by more than 10% twice.  Where it matters (in place / decoded): gate|up
+// gated at 129 rows 91 / 125 us, at 300 176 / 148, at 2048 530 / 395; 2 x 8192 x
+// 3072 gated at 512 rows 75 / 87, at 768 136 / 110; 2 x 13824 x 5120 at 256 rows
+// 164 / 215; 8192 x 1024 at 256 14 / 24; 4096 x 4096 at 129 44 / 39.
+bool fg_pays(const spl_matrix* const* W, int count, int64_t M, bool gated) {
+  int64_t N[SPL_MAX_GROUP], bytes = 0, kmax = 0;
+  double inplace = 0;
+  if (W[0]->dtype == SPL_I8) {
+    const int64_t small = ((W[0]->rows + 63) / 64) * ((M + 127) / 128);
+    return count > 1 || W[0]->cols > 1024 || small > device_cus();
+  }
+  for (int i = 0; i < count; ++i) {
+    const int64_t K = W[i]->cols;
+    N[i] = W[i]->rows;
+    bytes += fg_bytes<false>(W[i]->rows, K);
+    kmax = K > kmax ? K : kmax;
+    if (!gated) inplace += fg_inplace_us(N[i], K, M);
+  }
+  if (gated) {
+    N[0] *= 2, count = 1;
+    inplace = fg_inplace_us(N[0], kmax, M);
+  }
+  return inplace >= 16 && fg_decoded_us(N, count, kmax, M, bytes, gated) < inplace;
 }
 
 template <class T, int kMode, bool kRagged>
 hipError_t fg_product_r(FgGroupArg& g, hipStream_t s) {
-  switch (fg_tile(g, kMode == kFgGated)) {
+  int64_t N[SPL_MAX_GROUP];
+  for (int i = 0; i < g.count; ++i) N[i] = g.t[i].N * (kMode == kFgGated ? 2 : 1);
+  switch (fg_cost(N, g.count, g.M).tile) {
     case kFgL:
       // (eight waves for int8, whose MFMAs the compiler keeps off the accumulation registers)
       if constexpr (!kRagged && fg_q<T>()) return fg_launch<T, 4, 4, 2, 4, kMode, kRagged>(g, s);
@@ -587,7 +645,7 @@ int64_t fg_groups(int64_t M, int64_t rows) { return ((rows + 63) / 64) * ((M + 1
 
 }  // namespace
 
-int64_t frag_linear_bytes(const spl_matrix* const* W, int count, int64_t M) {
+int64_t frag_linear_bytes(const spl_matrix* const* W, int count, int64_t M, bool gated) {
   int64_t bytes = 0, groups = 0;
   for (int i = 0; i < count; ++i) {
     const bool q = W[i]->dtype == SPL_I8;
@@ -595,7 +653,7 @@ int64_t frag_linear_bytes(const spl_matrix* const* W, int count, int64_t M) {
     if (!(q ? fg_fits<true>(M, W[i]->rows, W[i]->cols) : fg_fits<false>(M, W[i]->rows, W[i]->cols))) return 0;
     if (W[i]->nnz > 0) bytes += q ? fg_bytes<true>(W[i]->rows, W[i]->cols) : fg_bytes<false>(W[i]->rows, W[i]->cols);
   }
-  return groups <= kFgMaxGroups ? bytes : 0;
+  return groups <= kFgMaxGroups && fg_pays(W, count, M, gated) ? bytes : 0;
 }
 
 hipError_t launch_frag_linear(const spl_sparse_task* tasks, int count, int64_t M, void* scratch, hipStream_t s) {
@@ -667,7 +725,13 @@ hipError_t launch_frag_int8(const spl_int8_task* tasks, int count, int64_t M, vo
 int64_t frag_input_grad_bytes(const spl_matrix& W, int64_t M) {
   if (W.rows % 8 != 0 || !fg_fits<false>(M, 32 * tile_steps(W.cols), W.rows) || fg_groups(M, W.cols) > kFgMaxGroups)
     return 0;
-  return 2 * tile_steps(W.cols) * fg_steps<false>(W.rows) * 1024;
+  const int64_t bytes = 2 * tile_steps(W.cols) * fg_steps<false>(W.rows) * 1024;
+  // Where W's packed tiles can be read directly, decoding them first has to be the faster way (512 x 4096 at 2048 rows
+  // 24 us decoded, 20 directly; 4096 x 4096 70, 95); elsewhere the other way decodes and transposes all of W.
+  if (sparse_input_grad_applies(M, W) &&
+      fg_decoded_us(&W.cols, 1, W.rows, M, bytes, false) >= fg_inplace_us(W.cols, W.rows, M))
+    return 0;
+  return bytes;
 }
 
 hipError_t launch_frag_input_grad(const void* dY, int64_t M, const spl_matrix& W, void* dX, void* scratch,

@@ -294,7 +294,7 @@ static int64_t linear_scratch(const spl_sparse_task* tasks, int32_t count, int64
   const spl_matrix* W[SPL_MAX_GROUP];
   if (M <= spl::kWideMaxM) return 0;
   for (int32_t i = 0; i < count; ++i) W[i] = tasks[i].W;
-  return spl::frag_linear_bytes(W, count, M);
+  return spl::frag_linear_bytes(W, count, M, false);
 }
 
 static spl_status check_sparse_group(const spl_sparse_task* tasks, int32_t count, int64_t M) {
@@ -328,7 +328,7 @@ spl_status spl_sparse_linear_group_scratch(const spl_sparse_task* tasks, int32_t
 static int64_t gated_scratch(int64_t M, const spl_matrix* Wgate, const spl_matrix* Wup) {
   if (M <= kGatedWideMaxM) return 0;
   const spl_matrix* W[2] = {Wgate, Wup};
-  return spl::frag_linear_bytes(W, 2, M);
+  return spl::frag_linear_bytes(W, 2, M, true);
 }
 
 int64_t spl_sparse_linear_silu_mul_scratch_bytes(int64_t M, const spl_matrix* Wgate, const spl_matrix* Wup) {
@@ -654,7 +654,7 @@ static int64_t int8_scratch(const spl_int8_task* tasks, int32_t count, int64_t M
   const spl_matrix* W[SPL_MAX_GROUP];
   if (M < spl::kI8PrefillMinM) return 0;
   for (int32_t i = 0; i < count; ++i) W[i] = tasks[i].Wq;
-  return spl::frag_linear_bytes(W, count, M);
+  return spl::frag_linear_bytes(W, count, M, false);
 }
 
 static spl_status check_int8_group(const spl_int8_task* tasks, int32_t count, int64_t M) {

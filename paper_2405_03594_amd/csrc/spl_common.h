@@ -227,14 +227,15 @@ hipError_t launch_int8_wide(const spl_int8_task* tasks, int count, int64_t M, hi
 // the decoded product) instead of the streaming ones.
 constexpr int64_t kI8PrefillMinM = 128;
 // Products through a decoded copy in scratch memory of frag_linear_bytes
-// (matrices of one kind, 16-bit or int8; 0: a matrix or batch is too large to
-// address), 256-byte aligned.  M >= 1.
-int64_t frag_linear_bytes(const spl_matrix* const* W, int count, int64_t M);
+// (matrices of one kind, 16-bit or int8; gated: the gate and the up matrix; 0:
+// a matrix or batch is too large to address, or the kernels that expand in
+// place are the faster ones), 256-byte aligned.  M >= 1.
+int64_t frag_linear_bytes(const spl_matrix* const* W, int count, int64_t M, bool gated);
 hipError_t launch_frag_linear(const spl_sparse_task* tasks, int count, int64_t M, void* scratch, hipStream_t s);
 hipError_t launch_frag_gated(const void* X, int64_t M, const spl_matrix& Wg, const spl_matrix& Wu, void* Y,
                              void* scratch, hipStream_t s);
 hipError_t launch_frag_int8(const spl_int8_task* tasks, int count, int64_t M, void* scratch, hipStream_t s);
-// dX = dY W through W's decoded transpose (0: W.rows % 8 != 0, or too large).
+// dX = dY W through W's decoded transpose (0: W.rows % 8 != 0, too large, or the direct kernel is the faster one).
 int64_t frag_input_grad_bytes(const spl_matrix& W, int64_t M);
 hipError_t launch_frag_input_grad(const void* dY, int64_t M, const spl_matrix& W, void* dX, void* scratch,
                                   hipStream_t s);

@@ -590,3 +590,46 @@ def test_scratch_belongs_to_the_stream_of_the_call(monkeypatch):
                             (d0, other, (other, d1)), (d0, Handle(), (Stream(0, 64), d0))):
         assert spl._scratch(16, device, s) == (16,)
         assert got.pop() == want, (device, s and s.cuda_stream)
+
+
+def test_scratch_is_offered_where_decoding_first_is_faster(L):
+    """The size functions return 0 where the kernels that expand in place were measured to be the faster ones."""
+    from paper_2405_03594_amd import _Int8Task, _SparseTask
+
+    def mat(n, k, dtype=2):
+        return _mat(rows=n, cols=k, dtype=dtype, layout=1, tile_offsets=0x40000)
+
+    def group(m, *shapes):
+        mats = [mat(n, k) for n, k in shapes]
+        t = (_SparseTask * len(mats))(*[_SparseTask(0x40000, ctypes.pointer(x), 0x50000) for x in mats])
+        return L.spl_sparse_linear_group_scratch_bytes(t, len(mats), m)
+
+    def gated(m, n, k):
+        g, u = mat(n, k), mat(n, k)
+        return L.spl_sparse_linear_silu_mul_scratch_bytes(m, ctypes.byref(g), ctypes.byref(u))
+
+    def int8(m, *shapes):
+        mats = [mat(n, k, 3) for n, k in shapes]
+        t = (_Int8Task * len(mats))(*[_Int8Task(0x40000, 0x60000, ctypes.pointer(x), 0x70000, 0x50000, None)
+                                      for x in mats])
+        return L.spl_sparse_linear_int8_group_scratch_bytes(t, len(mats), m)
+
+    frag = lambda n, k, per: (n + 15) // 16 * 2 * ((k + 2 * per - 1) // (2 * per)) * 1024
+    assert group(128, (4096, 4096)) == 0                        # the streaming kernel's
+    assert group(129, (4096, 4096)) == frag(4096, 4096, 32)
+    assert group(397, *[(4096, 4096)] * 3) == 3 * frag(4096, 4096, 32)
+    for m in (129, 512, 2048):
+        assert group(m, (1024, 1024)) == group(m, (768, 768)) == 0
+    assert group(256, (8192, 1024)) == 0
+    assert group(256, *[(13824, 5120)] * 2) == 0
+    assert group(397, *[(13824, 5120)] * 2) > 0
+    for m, big in ((113, 0), (129, 0), (256, 0), (300, 1), (2048, 1)):
+        assert (gated(m, 11008, 4096) > 0) == big, m
+    assert gated(512, 8192, 3072) == 0 and gated(768, 8192, 3072) == 2 * frag(8192, 3072, 32)
+    assert gated(1024, 2048, 768) == 0
+    grad = lambda m, n, k: L.spl_sparse_input_grad_scratch_bytes(m, ctypes.byref(mat(n, k)))
+    assert grad(2048, 512, 4096) == 0 and grad(2048, 4096, 4096) == frag(4096, 4096, 32)
+    assert grad(2000, 512, 4096) == frag(4096, 512, 32)         # the direct kernel does not apply
+    assert int8(127, (4096, 4096)) == int8(129, (1024, 1024)) == 0
+    assert int8(129, (4096, 4096)) == frag(4096, 4096, 64)
+    assert int8(129, *[(1024, 1024)] * 3) == 3 * frag(1024, 1024, 64)

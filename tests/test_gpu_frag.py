@@ -8,7 +8,9 @@ workgroup's tile, outputs whose rows are not whole 16-byte pieces, columns
 short of a stage, one to six stages (the loop takes four at a time), the last
 batch row of a tile and the first of the next, and each workgroup tile (64 x
 128 for the small grids; the larger ones are chosen by the grids below on a
-device of 256 CUs)."""
+device of 256 CUs).  Calls too small to gain are expanded in place, so that
+narrow matrices are run as groups of four (int8: two); every test asserts that
+its calls are offered scratch."""
 import ctypes
 
 import numpy as np
@@ -36,6 +38,13 @@ def _packed(spl, W, mask, dtype):
     return spl.pack_sparse(to_dev(W, dtype), torch.from_numpy(mask).cuda())
 
 
+def _group_scratch(spl, Xs, mats, outs):
+    views = [m.view() for m in mats]
+    tasks = (spl._SparseTask * len(mats))(*[spl._SparseTask(x.data_ptr(), ctypes.pointer(v), o.data_ptr())
+                                            for x, v, o in zip(Xs, views, outs)])
+    return spl.lib().spl_sparse_linear_group_scratch_bytes(tasks, len(mats), Xs[0].shape[0])
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("N,K,s", [(1, 8, 0.5), (16, 64, 0.7), (40, 72, 0.5), (72, 136, 0.0), (130, 200, 0.7),
                                    (300, 320, 0.7), (33, 1000, 0.5), (17, 264, 1.0)])
@@ -47,20 +56,26 @@ def test_frag_linear(orc, spl, dtype, N, K, s):
     ref = orc.linear_f64(X, orc.pack(W, dtype, mask))
     Wc, Xd = _packed(spl, W, mask, dtype), to_dev(X, dtype)
     for M in BATCHES:
-        out = torch.full((M + 1, N), 7.0, dtype=Xd.dtype, device="cuda")
-        spl.sparse_linear(Xd[:M].contiguous(), Wc, out=out[:M])
-        assert_close(from_dev_f64(out[:M]), ref[:M], f"{dtype} N={N} K={K} M={M}")
-        assert (out[M] == 7.0).all(), "written past the output"
+        x = Xd[:M].contiguous()
+        outs = [torch.full((M + 1, N), 7.0, dtype=Xd.dtype, device="cuda") for _ in range(4)]
+        assert _group_scratch(spl, [x] * 4, [Wc] * 4, outs) > 0 or Wc.nnz == 0
+        spl.sparse_linear_group([x] * 4, [Wc] * 4, [o[:M] for o in outs])
+        for out in outs:
+            assert_close(from_dev_f64(out[:M]), ref[:M], f"{dtype} N={N} K={K} M={M}")
+            assert (out[M] == 7.0).all(), "written past the output"
 
 
 # 16 x 16 tiles of 128 x 256 fill 256 CUs once; 256 of 128 x 128 leave one per CU; both on whole and ragged stages
-@pytest.mark.parametrize("N,M,K", [(2048, 4096, 128), (2040, 4090, 128), (2048, 2048, 192), (2048, 2048, 72)])
-def test_frag_tiles(orc, spl, N, M, K):
+@pytest.mark.parametrize("N,M,K", [(2048, 4096, 1536), (2040, 4090, 1536), (2048, 2048, 1600), (2048, 2048, 1608)])
+def test_frag_tiles(spl, N, M, K):
+    import torch
+
     W, mask = synth.weight(50 + K, N, K, "bf16", 0.7)
-    X = synth.activations(51 + K, M, K, "bf16")
-    ref = orc.linear_f64(X, orc.pack(W, "bf16", mask))
-    assert_close(from_dev_f64(spl.sparse_linear(to_dev(X, "bf16"), _packed(spl, W, mask, "bf16"))), ref,
-                 f"N={N} M={M} K={K}")
+    X, Wc = to_dev(synth.activations(51 + K, M, K, "bf16"), "bf16"), _packed(spl, W, mask, "bf16")
+    assert _group_scratch(spl, [X], [Wc], [X]) > 0
+    dense = to_dev(W, "bf16").double() * torch.from_numpy(mask).cuda()
+    ref = X.double() @ dense.t().contiguous()
+    assert_close(from_dev_f64(spl.sparse_linear(X, Wc)), ref.cpu().numpy(), f"N={N} M={M} K={K}")
 
 
 def test_frag_group_and_scratch_limits(orc, spl):
@@ -96,13 +111,14 @@ def test_frag_group_and_scratch_limits(orc, spl):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("N,K,s", [(20, 72, 0.7), (70, 200, 0.5), (264, 128, 0.6)])
+@pytest.mark.parametrize("N,K,s", [(20, 1608, 0.7), (70, 1736, 0.5), (264, 1664, 0.6)])
 def test_frag_gated(orc, spl, dtype, N, K, s):
     (Wg, mg), (Wu, mu) = (synth.weight(80 + i + N, N, K, dtype, s) for i in range(2))
     X = synth.activations(82 + K, max(BATCHES), K, dtype)
     ref = orc.silu_mul_f64(X, orc.pack(Wg, dtype, mg), orc.pack(Wu, dtype, mu))
     g, u, Xd = _packed(spl, Wg, mg, dtype), _packed(spl, Wu, mu, dtype), to_dev(X, dtype)
     for M in [113] + BATCHES:
+        assert spl.lib().spl_sparse_linear_silu_mul_scratch_bytes(M, ctypes.byref(g.view()), ctypes.byref(u.view())) > 0
         assert_close(from_dev_f64(spl.sparse_linear_silu_mul(Xd[:M].contiguous(), g, u)), ref[:M],
                      f"{dtype} N={N} K={K} M={M}")
 
@@ -115,11 +131,18 @@ def test_frag_int8(orc, spl, N, K, M, s):
     Wq, mask, sw = synth.int8_weight(90 + N, N, K, s)
     Xq, sx = synth.int8_activations(91 + K, M, K)
     acc_ref, y_ref = orc.linear_i8(Xq, sx, orc.pack(Wq, "i8", mask), sw)
-    acc = torch.empty((M, N), dtype=torch.int32, device="cuda")
-    Y = spl.sparse_linear_int8(to_dev(Xq, "i8"), torch.from_numpy(sx).cuda(), _packed(spl, Wq, mask, "i8"),
-                               torch.from_numpy(sw).cuda(), acc_out=acc)
-    assert np.array_equal(acc.cpu().numpy(), acc_ref)
-    assert np.array_equal(Y.cpu().view(torch.int16).numpy().view(np.uint16), y_ref)
+    n = 1 if N > 1000 else 2                    # one small matrix is expanded in place
+    accs = [torch.empty((M, N), dtype=torch.int32, device="cuda") for _ in range(n)]
+    Xd, sxd, swd, Wc = to_dev(Xq, "i8"), torch.from_numpy(sx).cuda(), torch.from_numpy(sw).cuda(), _packed(spl, Wq, mask,
+                                                                                                          "i8")
+    Ys = spl.sparse_linear_int8_group([Xd] * n, [sxd] * n, [Wc] * n, [swd] * n, acc_outs=accs)
+    view = Wc.view()
+    tasks = (spl._Int8Task * n)(*[spl._Int8Task(Xd.data_ptr(), sxd.data_ptr(), ctypes.pointer(view), swd.data_ptr(),
+                                                y.data_ptr(), None) for y in Ys])
+    assert spl.lib().spl_sparse_linear_int8_group_scratch_bytes(tasks, n, M) > 0
+    for acc, Y in zip(accs, Ys):
+        assert np.array_equal(acc.cpu().numpy(), acc_ref)
+        assert np.array_equal(Y.cpu().view(torch.int16).numpy().view(np.uint16), y_ref)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
@@ -138,9 +161,10 @@ def test_frag_graph_replays_and_streams(spl):
     """Scratch from the graph's pool, and from another stream's pool, gives the eager result."""
     import torch
 
-    W, mask = synth.weight(7, 512, 640, "bf16", 0.7)
-    Wc, X = _packed(spl, W, mask, "bf16"), to_dev(synth.activations(8, 300, 640, "bf16"), "bf16")
+    W, mask = synth.weight(7, 512, 2048, "bf16", 0.7)
+    Wc, X = _packed(spl, W, mask, "bf16"), to_dev(synth.activations(8, 300, 2048, "bf16"), "bf16")
     eager = spl.sparse_linear(X, Wc)
+    assert _group_scratch(spl, [X], [Wc], [eager]) > 0
     torch.cuda.synchronize()
     side = torch.cuda.Stream()
     other = torch.empty_like(eager)

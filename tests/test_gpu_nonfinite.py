@@ -40,7 +40,7 @@ def _same_kind(Y, ref, what):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("N,K,s", [(33, 136, 0.5), (2050, 1096, 0.7)])
+@pytest.mark.parametrize("N,K,s", [(33, 136, 0.5), (2050, 1608, 0.7)])
 def test_nonfinite_linear(spl, dtype, N, K, s):
     import torch
 
