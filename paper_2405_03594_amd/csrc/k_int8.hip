@@ -6,22 +6,8 @@
 //   Y[m][n] = fp16_rne( (float(acc) * sx[m]) * sw[n] )
 // with each product rounded to binary32 (no fused multiply-add).
 //
-// Sparse kernel (the decode kernel's design with 1-byte payloads): a
-// workgroup owns one 16-row block and its waves split the block's tile pairs
-// into contiguous ranges.  One MFMA covers a pair of consecutive 16 x 32
-// tiles: lanes 0-31 take tile s, lanes 32-63 tile s + 1, lane (fr, fg) row fr,
-// columns 16 (fg % 2) .. +16 of its tile.  A wave stages a chunk of tiles
-// (whole pairs, as many as fit a 3 KB buffer) with aligned 16-byte loads in
-// LDS, the tile offsets of its whole range come with one load, and the next
-// chunk is in flight while the current one is multiplied.  Each lane expands
-// its four 4-column nibbles: a tile's values are stored by 16-column group,
-// then row, i.e. in the order of the tile's 32 lanes, so the nibble's values
-// start at the tile offset + the kept count of the lanes before (a 32-lane
-// DPP scan) + the nibbles before it, are read as an aligned dword pair realigned with
-// v_alignbyte_b32, and a 16-entry selector table (conflict-free) drives
-// v_perm_b32 (paper section 2.4.1).  Activations of small batches are staged
-// in LDS once per workgroup; int32 partial sums of the waves are added in LDS
-// (integer addition: the order does not matter).
+// This file: where the sparse layer's launches go (k_int8_quad.hip, k_wide.hip,
+// k_prefill.hip), the dense comparator and the activations' quantizer.
 #include "spl_common.h"
 
 namespace spl {
@@ -30,16 +16,9 @@ namespace {
 constexpr int kI8Waves = 8;                 // dense kernel
 constexpr int kI8Threads = 64 * kI8Waves;
 constexpr int kI8Unroll = 4;                // dense kernel: 64-column steps per wave per group
-constexpr int kI8Chunk = 8;                 // sparse: at most this many tiles (4 pairs) per chunk (4 when M > 32)
-constexpr int kI8VBuf = 3072;               // staged value bytes per wave and chunk
-constexpr int kI8VBufAlloc = kI8VBuf + 16;  // + room past the last window
-constexpr int kI8PieceRounds = kI8VBuf / 16 / kWave;
-constexpr int kI8XLdsMax = 32 * 1024;       // activations staged in LDS when M * 64 ceil(S/2) bytes fit
-constexpr int kI8OffsetLanes = kWave - 1;
-// Batches of more rows than one batch fragment go to the streaming kernel that stages activations through
-// LDS, where it can address them: per launch, this file's kernel / that one, q|k|v 16.8 / 12.4 us at 17
-// rows, 18.2 / 12.9 at 24, 20.2 / 13.8 at 32, 55.4 / 25.4 at 127; gate|up 27.7 / 20.2, 30.9 / 20.4, 34.7 /
-// 21.3, 97.6 / 46.2; down 13.4 / 12.1, 16.0 / 12.3, 17.6 / 12.9, 48.7 / 33.7.
+constexpr int64_t kI8MaxBytes = (int64_t)1 << 31;   // activations of one launch
+// Batches of more rows than one batch fragment go to the streaming kernel (q|k|v 12.4 us a launch at 17 rows, 13.8 at
+// 32, 25.4 at 127; gate|up 20.2, 21.3, 46.2).
 constexpr int64_t kI8WideMinM = 17;
 // On up to one row block per CU, where the four-tile kernel waits for its activations most, from 12 rows, or 16 past
 // 4096 columns: its launches / the streaming ones at 12, 14 and 16 rows 3072 x 3072 5.8 / 5.4, 5.9 / 5.4, 6.1 / 5.4
@@ -83,49 +62,6 @@ __device__ __forceinline__ void i8_finish(const i32x4 (&acc)[MT], int32_t* part,
   }
 }
 
-// int8 activations staged in LDS: rows of 64 * ceil(S / 2) + 16 bytes (whole
-// tile pairs, so the second tile of a last half pair reads zeros), zero past
-// K.  Lanes of padding batch rows read a 64-byte zero area and do not advance.
-__host__ __device__ __forceinline__ int64_t i8_xs_stride(int64_t K) { return 64 * ((tile_steps(K) + 1) / 2) + 16; }
-
-template <int W>
-__device__ __forceinline__ void i8_stage_x(uint8_t* xs, const int8_t* __restrict__ X, int M, int64_t K) {
-  const int per_row = (int)(4 * ((tile_steps(K) + 1) / 2));   // 16-byte pieces per staged row (whole pairs)
-  const int kp = (int)(K / 16);                           // pieces holding activations
-  const int total = M * per_row;
-  for (int p = threadIdx.x; p < total; p += W * kWave) {
-    const int m = p / per_row, q = p - m * per_row;
-    u32x4 v = u32x4{0u, 0u, 0u, 0u};
-    if (q < kp) v = *reinterpret_cast<const u32x4*>(X + (int64_t)m * K + 16 * q);
-    *reinterpret_cast<u32x4*>(xs + (int64_t)m * i8_xs_stride(K) + 16 * q) = v;
-  }
-}
-
-struct I8Chunk {
-  int cn;
-  uint32_t a0;
-  int np;
-};
-
-// Grouped launches: task i owns the row blocks [first[i], first[i + 1]) of the
-// grid's x dimension; every task has the group's batch M (grid y).
-struct I8TaskArg {
-  const int8_t* Xq;
-  const float* sx;
-  const uint32_t* bm;
-  const uint8_t* values;
-  const int32_t* toff;
-  int64_t N, K;
-  const float* sw;
-  uint16_t* Y;
-  int32_t* acc;
-};
-struct I8GroupArg {
-  I8TaskArg t[SPL_MAX_GROUP];
-  int32_t first[SPL_MAX_GROUP + 1];
-  int32_t count;
-  int32_t M;
-};
 struct I8DenseTaskArg {
   const int8_t* Xq;
   const float* sx;
@@ -141,204 +77,6 @@ struct I8DenseGroupArg {
   int32_t count;
   int32_t M;
 };
-
-template <int MT, bool XL, int W>
-__global__ void __launch_bounds__(W * kWave, XL ? 8 : 4) k_sparse_int8(const I8GroupArg g) {
-  const int ti = find_task(g.first, g.count);
-  const I8TaskArg tk = g.t[ti];
-  const int8_t* __restrict__ Xq = tk.Xq;
-  const float* __restrict__ sx = tk.sx;
-  const int64_t M = g.M, K = tk.K, N = tk.N;
-  const uint32_t* __restrict__ bm_tiles = tk.bm;
-  const uint8_t* __restrict__ values = tk.values;
-  const int32_t* __restrict__ tile_offsets = tk.toff;
-  const float* __restrict__ sw = tk.sw;
-  uint16_t* __restrict__ Y = tk.Y;
-  int32_t* __restrict__ acc_out = tk.acc;
-  constexpr int C = MT == 4 ? kI8Chunk / 2 : kI8Chunk;     // four batch fragments: half the operands in flight
-  extern __shared__ __align__(16) unsigned char dsm[];     // value buffers (later the partial sums), then X
-  __shared__ uint32_t lut[16];
-  __shared__ u32x4 xzero[4];
-  // per wave: [row][tile of the chunk]; the odd row stride C + 1 puts the 16 rows in distinct banks
-  constexpr int WS = C + 1;
-  __shared__ __align__(16) uint32_t words[W][16 * WS];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int fr = lane & 15, fg = lane >> 4;
-  const int tsel = fg >> 1, half = fg & 1;
-  const int64_t blk = (int64_t)blockIdx.x - g.first[ti];
-  const int64_t m0 = (int64_t)blockIdx.y * 16 * MT;
-  const int S = (int)tile_steps(K);
-  const int P = (S + 1) / 2;
-  // this wave's tiles: whole pairs [2 pb, 2 pe) clipped to S
-  int kbeg, kend;
-  {
-    const int Lp = (P + W - 1) / W;
-    const int pb = wave * Lp < P ? wave * Lp : P;
-    const int pe = pb + Lp < P ? pb + Lp : P;
-    kbeg = 2 * pb;
-    kend = 2 * pe < S ? 2 * pe : S;
-    if (kbeg > kend) kbeg = kend;
-  }
-  const size_t vbytes_region = (size_t)W * kI8VBufAlloc > (size_t)W * MT * 1024 ? (size_t)W * kI8VBufAlloc
-                                                                                  : (size_t)W * MT * 1024;
-  unsigned char* vbuf = dsm + wave * kI8VBufAlloc;
-  uint8_t* xs = reinterpret_cast<uint8_t*>(dsm + vbytes_region);
-  const uint32_t* bmb = bm_tiles + blk * S * 16;
-  const int32_t* tob = tile_offsets + blk * S;
-  uint32_t* wl = words[wave];
-
-  int ob = kbeg;
-  auto load_offsets = [&](int base) {
-    const int t = base + lane < kend ? base + lane : kend;
-    return tob[t];
-  };
-  // whole pairs that fit the staging buffer (1-byte values: offsets are byte positions)
-  auto shape = [&](int32_t o, int c0) {
-    I8Chunk ch;
-    const int r = c0 - ob;
-    ch.a0 = (uint32_t)__builtin_amdgcn_readlane(o, r) & ~15u;
-    const uint32_t lim = ch.a0 + kI8VBuf;
-    const int jmax = kend - c0 < C ? kend - c0 : C;
-    const bool fit = lane >= r + 1 && lane <= r + jmax && (uint32_t)o <= lim;
-    int cn = __builtin_popcountll(__ballot(fit));          // >= 2 when jmax >= 2: two tiles are at most 1 KB
-    if (cn < jmax) cn &= ~1;                                // chunks end on a pair boundary, or at the range end
-    ch.cn = cn;
-    const uint32_t end = (uint32_t)__builtin_amdgcn_readlane(o, r + cn);
-    ch.np = (int)((end - ch.a0 + 15u) >> 4);
-    return ch;
-  };
-  u32x4 vp[kI8PieceRounds];
-  uint32_t wv[C / 4];
-  auto issue = [&](const I8Chunk& ch, int c0) {
-#pragma unroll
-    for (int r = 0; r < kI8PieceRounds; ++r) {
-      vp[r] = u32x4{0u, 0u, 0u, 0u};
-      const uint32_t off = ch.a0 + 16u * (uint32_t)(lane + kWave * r);
-      if (lane + kWave * r < ch.np) vp[r] = *reinterpret_cast<const u32x4*>(values + off);
-    }
-#pragma unroll
-    for (int i = 0; i < C / 4; ++i) {
-      wv[i] = 0u;
-      const uint32_t wi = (uint32_t)(c0 + fg + 4 * i) * 16u + (uint32_t)fr;
-      if (fg + 4 * i < ch.cn) wv[i] = bmb[wi];
-    }
-  };
-
-  int32_t orng = 0;
-  I8Chunk ch{0, 0u, 0};
-  if (kbeg < kend) {
-    orng = load_offsets(ob);
-    ch = shape(orng, kbeg);
-    issue(ch, kbeg);
-  }
-  if (threadIdx.x < 16) lut[threadIdx.x] = nibble_selector8(threadIdx.x);
-  if (threadIdx.x < 4) xzero[threadIdx.x] = u32x4{0u, 0u, 0u, 0u};
-  if constexpr (XL) i8_stage_x<W>(xs, Xq, (int)M, K);
-  __syncthreads();
-
-  // activation operands: staged (XL) or direct
-  uint32_t xaddr0 = 0, xstep = 0;
-  if constexpr (XL) {
-    const bool live = fr < M;
-    xaddr0 = live ? lds_off(xs + (int64_t)fr * i8_xs_stride(K) + 16 * fg) : lds_off(xzero + fg);
-    xstep = live ? 64u : 0u;
-  }
-  const int8_t* xrow[MT];
-  bool xlive[MT];
-#pragma unroll
-  for (int t = 0; t < MT; ++t) {
-    const int64_t m = m0 + 16 * t + fr;
-    xlive[t] = m < M;
-    xrow[t] = Xq + (xlive[t] ? m : 0) * K + 16 * fg;
-  }
-  const uint32_t lut_addr = lds_off(lut);
-  const uint32_t vbuf_addr = lds_off(vbuf);
-  u32x4 xs_op = u32x4{0u, 0u, 0u, 0u};
-
-  i32x4 acc[MT];
-#pragma unroll
-  for (int t = 0; t < MT; ++t) acc[t] = i32x4{0, 0, 0, 0};
-
-  for (int c0 = kbeg; c0 < kend;) {
-    // 1. stage the current chunk
-#pragma unroll
-    for (int r = 0; r < kI8PieceRounds; ++r)
-      if (lane + kWave * r < ch.np) *reinterpret_cast<u32x4*>(vbuf + 16 * (lane + kWave * r)) = vp[r];
-#pragma unroll
-    for (int i = 0; i < C / 4; ++i) wl[fr * WS + fg + 4 * i] = wv[i];
-    wave_lds_sync();
-    const I8Chunk cur = ch;
-    int32_t tc[C];
-#pragma unroll
-    for (int j = 0; j < C; ++j) tc[j] = __builtin_amdgcn_readlane(orng, c0 - ob + j);
-
-    // 2. direct activations for this chunk, then the next chunk's loads
-    u32x4 xb[XL ? 1 : C / 2][MT];
-    if constexpr (!XL) {
-#pragma unroll
-      for (int q = 0; q < C / 2; ++q)
-#pragma unroll
-        for (int t = 0; t < MT; ++t) {
-          const int64_t k = 32 * (int64_t)(c0 + 2 * q) + 16 * fg;
-          xb[q][t] = u32x4{0u, 0u, 0u, 0u};
-          if (2 * q < cur.cn && k < K && xlive[t]) xb[q][t] = *reinterpret_cast<const u32x4*>(xrow[t] + 32 * (int64_t)(c0 + 2 * q));
-        }
-    }
-    const int c1 = c0 + cur.cn;
-    if (c1 < kend) {
-      if (c1 - ob + C > kI8OffsetLanes) {
-        ob = c1;
-        orng = load_offsets(ob);
-      }
-      ch = shape(orng, c1);
-      issue(ch, c1);
-    }
-
-    // 3. expand and multiply, one tile pair per MFMA
-    const uint32_t vrel = vbuf_addr - cur.a0;
-#pragma unroll
-    for (int q = 0; q < C / 2; ++q) {
-      if (2 * q < cur.cn) {
-        const int j = 2 * q + tsel;                            // this lane's tile in the chunk
-        uint32_t w = wl[fr * WS + j];
-        if (j >= cur.cn) w = 0u;                               // a range ending on half a pair
-        // values stored before mine in my tile: a tile's values are ordered by 16-column group (my
-        // half), then row (my fr), i.e. in the order of the tile's 32 lanes, so this is the
-        // exclusive scan of the kept counts over my half of the wave
-        const uint32_t pc = __popc(__builtin_amdgcn_ubfe(w, 16 * half, 16));
-        const uint32_t before = half_inclusive_scan(pc) - pc;
-        // this lane's tile offset: the pair's first or second (arithmetic select keeps tc[] in registers)
-        const uint32_t tile0 = (uint32_t)tc[2 * q] + (((uint32_t)tc[2 * q + 1] - (uint32_t)tc[2 * q]) & (0u - (uint32_t)tsel));
-        const uint32_t oa = tile0 + before;
-        u32x4 a;
-        uint32_t o = oa;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const uint32_t nib = __builtin_amdgcn_ubfe(w, 16 * half + 4 * i, 4);
-          const uint32_t p = o + vrel;
-          const uint32_t d = p & ~3u;
-          const uint32_t lo = lds_load4(d), hi = lds_load4(d + 4);
-          const uint32_t win = __builtin_amdgcn_alignbyte(hi, lo, p);
-          const uint32_t sel = lds_load4(lut_addr + 4u * nib);
-          a[i] = __builtin_amdgcn_perm(0u, win, sel);
-          o += __popc(nib);
-        }
-        if constexpr (XL) {
-          if (xstep) xs_op = lds_load16(xaddr0 + xstep * (uint32_t)((c0 >> 1) + q));
-          acc[0] = mfma_i8(a, xs_op, acc[0]);
-        } else {
-#pragma unroll
-          for (int t = 0; t < MT; ++t) acc[t] = mfma_i8(a, xb[q][t], acc[t]);
-        }
-      }
-    }
-    wave_lds_sync();
-    c0 = c1;
-  }
-  __syncthreads();
-  i8_finish<MT, W>(acc, reinterpret_cast<int32_t*>(dsm), wave, lane, blk * 16, N, m0, M, sx, sw, Y, acc_out);
-}
 
 template <int MT>
 __global__ void __launch_bounds__(kI8Threads) k_dense_int8(const I8DenseGroupArg g) {
@@ -397,31 +135,6 @@ __global__ void __launch_bounds__(kI8Threads) k_dense_int8(const I8DenseGroupArg
 }
 
 int i8_fragments(int64_t M) { return M <= 16 ? 1 : (M <= 32 ? 2 : 4); }
-
-template <int MT, bool XL, int W>
-hipError_t sparse_int8_launch(const I8GroupArg& g, int64_t kmax, hipStream_t s) {
-  auto* kernel = k_sparse_int8<MT, XL, W>;
-  const size_t region = (size_t)W * kI8VBufAlloc > (size_t)W * MT * 1024 ? (size_t)W * kI8VBufAlloc
-                                                                          : (size_t)W * MT * 1024;
-  const size_t xbytes = XL ? (size_t)g.M * (size_t)i8_xs_stride(kmax) : 0;
-  static PerDeviceFlag lds_set;
-  const hipError_t attr = allow_lds_once(lds_set, kernel, region + (XL ? kI8XLdsMax + 16 * 16 : 0));
-  if (attr != hipSuccess) return attr;
-  const dim3 grid((unsigned)g.first[g.count], (unsigned)((g.M + 16 * MT - 1) / (16 * MT)));
-  hipLaunchKernelGGL(kernel, grid, dim3(W * kWave), region + xbytes, s, g);
-  return hipGetLastError();
-}
-
-// Activations staged in LDS when every task's M x 64 ceil(S/2) bytes fit.
-template <int W>
-hipError_t sparse_int8_w(const I8GroupArg& g, int64_t kmax, hipStream_t s) {
-  const int MT = i8_fragments(g.M);
-  if (MT == 1 && (int64_t)g.M * 64 * ((tile_steps(kmax) + 1) / 2) <= kI8XLdsMax)
-    return sparse_int8_launch<1, true, W>(g, kmax, s);
-  if (MT == 1) return sparse_int8_launch<1, false, W>(g, kmax, s);
-  if (MT == 2) return sparse_int8_launch<2, false, W>(g, kmax, s);
-  return sparse_int8_launch<4, false, W>(g, kmax, s);
-}
 
 // Per-token activation quantisation (paper section 3.4 quantises the
 // activations to int8; symmetric, one binary32 scale per row): one workgroup
@@ -516,8 +229,6 @@ void quantize_rows_launch(const uint16_t* x, int64_t M, int64_t K, int8_t* Xq, f
     launch(k_quantize_rows<T, 0, 256>, 256);
 }
 
-bool i8_small_grid(int64_t blocks) { return blocks < 2 * (int64_t)device_cus(); }
-
 }  // namespace
 
 hipError_t launch_sparse_int8(const spl_int8_task* tasks, int count, int64_t M, hipStream_t s) {
@@ -536,24 +247,27 @@ hipError_t launch_sparse_int8(const spl_int8_task* tasks, int count, int64_t M, 
   bool wide = M >= kI8WideMinM || i8_wide_small(M, blocks, kmax);
   for (int i = 0; i < count; ++i) wide = wide && sparse_wide_fits(M, tasks[i].Wq->cols, 1);
   if (wide) return launch_int8_wide(tasks, count, M, s);
-  // Up to one batch fragment four tiles per scan, where 32 bits address the activations: launches of this file's
-  // kernel / that one at 1 and 8 rows 4096 x 4096 6.6 / 5.7, 7.0 / 6.0 us, q|k|v 11.0 / 9.8, 14.3 / 9.9, gate|up
-  // 16.7 / 14.8, 23.4 / 15.1.
+  // Up to one batch fragment four tiles per scan, where 32 bits address the activations: launches of the streaming
+  // kernel / that one at 8 rows 4096 x 4096 6.0 / 6.0 us, 4096 x 11008 9.8 / 9.8, q|k|v 10.4 / 9.9, gate|up 16.8 /
+  // 15.1.
   bool quad = M <= 16;
   for (int i = 0; i < count; ++i) quad = quad && int8_quad_fits(M, tasks[i].Wq->cols);
   if (quad) return launch_int8_quad(tasks, count, M, s);
-  I8GroupArg g{};
-  g.count = count;
-  g.M = (int32_t)M;
-  g.first[0] = 0;
-  for (int i = 0; i < count; ++i) {
-    const spl_matrix& W = *tasks[i].Wq;
-    g.t[i] = I8TaskArg{tasks[i].Xq, tasks[i].x_scales, W.bitmask, static_cast<const uint8_t*>(W.values),
-                       W.tile_offsets, W.rows, W.cols, tasks[i].w_scales, static_cast<uint16_t*>(tasks[i].Y),
-                       tasks[i].acc_out};
-    g.first[i + 1] = g.first[i] + (int32_t)tile_blocks(W.rows);
+  // Activations past 32-bit addressing: as many rows at a time as it takes.
+  const int64_t rows = kmax < kI8MaxBytes / M ? M : kI8MaxBytes / kmax;
+  for (int64_t m0 = 0; m0 < M; m0 += rows) {
+    spl_int8_task t[SPL_MAX_GROUP];
+    for (int i = 0; i < count; ++i) {
+      t[i] = tasks[i];
+      const int64_t N = t[i].Wq->rows;
+      t[i].Xq += m0 * t[i].Wq->cols, t[i].x_scales += m0;
+      t[i].Y = static_cast<uint16_t*>(t[i].Y) + m0 * N;
+      if (t[i].acc_out) t[i].acc_out += m0 * N;
+    }
+    const hipError_t e = launch_int8_wide(t, count, M - m0 < rows ? M - m0 : rows, s);
+    if (e != hipSuccess) return e;
   }
-  return i8_small_grid(blocks * ((M + 63) / 64)) ? sparse_int8_w<16>(g, kmax, s) : sparse_int8_w<8>(g, kmax, s);
+  return hipSuccess;
 }
 
 hipError_t launch_dense_int8(const spl_dense_int8_task* tasks, int count, int64_t M, hipStream_t s) {

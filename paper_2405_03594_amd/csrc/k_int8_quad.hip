@@ -7,8 +7,8 @@
 //   * lane (fr, fg) owns row fr of the quad's tile fg, and MFMA h multiplies
 //     column group h (16 columns) of the four tiles: one 4-step scan over the
 //     tile's 16 rows, the counts of both groups in one register, gives the
-//     first values of all eight operands of the quad's rows (the kernel there
-//     takes a 5-step scan per two tiles);
+//     first values of all eight operands of the quad's rows (k_wide.hip takes
+//     a 5-step scan per two tiles);
 //   * a wave loads a quad's values in 16-byte pieces and stages them in its own
 //     LDS (loads at the lanes' own starts, 20 bytes per group, take 64 cycles
 //     of the cache's address path each: four layers' step of one row 252 us
@@ -24,8 +24,8 @@
 //     wave's range, so nothing is clamped; words and offsets are two quads
 //     ahead, values and activations one.
 //
-// Four layers' step (hidden 4096, ffn 11008, 70%), k_int8.hip's kernel / this
-// one: 236 / 221 us at one row, 288 / 229 at 8, 285 / 264 at 16.
+// Four layers' step (hidden 4096, ffn 11008, 70%) with the kernel before, two
+// tiles per scan, / this one: 236 / 221 us at one row, 288 / 229 at 8.
 #include "spl_common.h"
 
 namespace spl {

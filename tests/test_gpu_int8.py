@@ -1,5 +1,7 @@
 """Sparse-quantized (int8 weights, int8 activations) linear layers on the GPU
 vs the oracle: int32 accumulators and fp16 outputs are compared bit for bit."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -25,6 +27,29 @@ def _run_sparse(spl, Xq, sx, Wq, mask, sw):
     acc = torch.empty((M, N), dtype=torch.int32, device="cuda")
     Y = spl.sparse_linear_int8(to_dev(Xq, "i8"), torch.from_numpy(sx).cuda(), Wqc, torch.from_numpy(sw).cuda(),
                                acc_out=acc)
+    return acc.cpu().numpy(), Y.cpu().view(torch.int16).numpy().view(np.uint16)
+
+
+def _plain_group(spl, Xqs, sxs, Wcs, sws, accs):
+    """The C entry point without scratch: what C callers run, and what the binding falls back to."""
+    import torch
+
+    M, n = Xqs[0].shape[0], len(Wcs)
+    outs = [torch.empty((M, w.rows), dtype=torch.float16, device="cuda") for w in Wcs]
+    views = [w.view() for w in Wcs]
+    tasks = (spl._Int8Task * n)(*[spl._Int8Task(x.data_ptr(), sx.data_ptr(), ctypes.pointer(v), sw.data_ptr(),
+                                                y.data_ptr(), a.data_ptr())
+                                  for x, sx, v, sw, y, a in zip(Xqs, sxs, views, sws, outs, accs)])
+    assert spl.lib().spl_sparse_linear_int8_group(tasks, n, M, torch.cuda.current_stream().cuda_stream) == 0
+    return outs
+
+
+def _run_plain(spl, Xq, sx, Wq, mask, sw):
+    import torch
+
+    Wqc = spl.pack_sparse(to_dev(Wq, "i8"), torch.from_numpy(mask).cuda())
+    acc = torch.empty((Xq.shape[0], Wq.shape[0]), dtype=torch.int32, device="cuda")
+    Y, = _plain_group(spl, [to_dev(Xq, "i8")], [torch.from_numpy(sx).cuda()], [Wqc], [torch.from_numpy(sw).cuda()], [acc])
     return acc.cpu().numpy(), Y.cpu().view(torch.int16).numpy().view(np.uint16)
 
 
@@ -158,9 +183,10 @@ def test_int8_epilogue_rounds_each_product(orc, spl, count):
 def test_int8_group_matches_oracle_and_single_calls(orc, spl, M):
     """A group of three layers with different N and K (one launch for all):
     every task's int32 sums and fp16 outputs equal the oracle and the single
-    calls bit for bit, sparse and dense (M = 1: staged activations; 16, 40,
-    70: one, two and four batch fragments, 70 on two batch blocks; 130: the
-    prefill tiling, one launch per task)."""
+    calls bit for bit, sparse, without scratch and dense (M = 1, 16: the
+    four-tile kernel, at 16 the streaming one; 40, 70: the streaming kernel,
+    70 on two batch blocks; 130: decoded fragments, without scratch the prefill
+    tiling, one launch per task)."""
     import torch
 
     shapes = [(40, 96, 0.7), (100, 528, 0.5), (33, 96, 0.9)]
@@ -176,10 +202,13 @@ def test_int8_group_matches_oracle_and_single_calls(orc, spl, M):
         dense.append(to_dev(np.where(mask.astype(bool), Wq, np.int8(0)), "i8"))
     accs = [torch.empty((M, N), dtype=torch.int32, device="cuda") for N, _, _ in shapes]
     outs = spl.sparse_linear_int8_group(Xqs, sxs, Wcs, sws, acc_outs=accs)
+    paccs = [torch.empty((M, N), dtype=torch.int32, device="cuda") for N, _, _ in shapes]
+    pouts = _plain_group(spl, Xqs, sxs, Wcs, sws, paccs)
     daccs = [torch.empty((M, N), dtype=torch.int32, device="cuda") for N, _, _ in shapes]
     douts = spl.dense_linear_int8_group(Xqs, sxs, dense, sws, acc_outs=daccs)
     for i, (acc_ref, y_ref) in enumerate(refs):
-        for what, acc, y in (("sparse", accs[i], outs[i]), ("dense", daccs[i], douts[i])):
+        for what, acc, y in (("sparse", accs[i], outs[i]), ("plain", paccs[i], pouts[i]),
+                             ("dense", daccs[i], douts[i])):
             _assert_equal(acc.cpu().numpy(), acc_ref, f"{what} group task {i} acc M={M}")
             _assert_equal(y.cpu().view(torch.int16).numpy().view(np.uint16), y_ref, f"{what} group task {i} Y M={M}")
         single = spl.sparse_linear_int8(Xqs[i], sxs[i], Wcs[i], sws[i])
@@ -197,16 +226,18 @@ def _sample_rows(M, seed, count=62):
 @pytest.mark.parametrize("N,K,s", [(1, 16, 0.5), (33, 64, 0.7), (130, 1008, 0.7), (64, 4096, 0.5), (200, 336, 0.0),
                                    (17, 512, 1.0), (48, 2064, 0.9), (300, 144, 0.5)])
 def test_int8_prefill_small(orc, spl, N, K, s):
-    """Batches of 128 rows and more take the MFMA-tiled prefill kernel: ragged
-    N, M and K (a partial last 128-byte stage) compared in full, bit for bit."""
+    """Batches of 128 rows and more take the MFMA-tiled prefill kernel, or
+    decoded fragments where the binding lends scratch: ragged N, M and K (a
+    partial last 128-byte stage) compared in full, bit for bit, both ways."""
     Wq, mask, sw = synth.int8_weight(620 + N, N, K, s)
     Xq, sx = synth.int8_activations(720 + K, max(PREFILL_I8_M), K)
     p = orc.pack(Wq, "i8", mask)
     for M in PREFILL_I8_M:
         acc_ref, y_ref = orc.linear_i8(Xq[:M], sx[:M], p, sw)
-        acc, y = _run_sparse(spl, Xq[:M], sx[:M], Wq, mask, sw)
-        _assert_equal(acc, acc_ref, f"acc N={N} K={K} s={s} M={M}")
-        _assert_equal(y, y_ref, f"Y N={N} K={K} s={s} M={M}")
+        for run in (_run_plain, _run_sparse):
+            acc, y = run(spl, Xq[:M], sx[:M], Wq, mask, sw)
+            _assert_equal(acc, acc_ref, f"acc N={N} K={K} s={s} M={M} {run.__name__}")
+            _assert_equal(y, y_ref, f"Y N={N} K={K} s={s} M={M} {run.__name__}")
 
 
 def _run_dense(spl, Xq, sx, Wd, sw):
@@ -227,9 +258,10 @@ def test_int8_prefill_grids(orc, spl, N, K, M, s):
     Wq, mask, sw = synth.int8_weight(950 + N, N, K, s)
     Xq, sx = synth.int8_activations(951 + K, M, K)
     acc_ref, y_ref = orc.linear_i8(Xq, sx, orc.pack(Wq, "i8", mask), sw)
-    acc, y = _run_sparse(spl, Xq, sx, Wq, mask, sw)
-    _assert_equal(acc, acc_ref, f"acc N={N} K={K} M={M}")
-    _assert_equal(y, y_ref, f"Y N={N} K={K} M={M}")
+    for run in (_run_plain, _run_sparse):
+        acc, y = run(spl, Xq, sx, Wq, mask, sw)
+        _assert_equal(acc, acc_ref, f"acc N={N} K={K} M={M} {run.__name__}")
+        _assert_equal(y, y_ref, f"Y N={N} K={K} M={M} {run.__name__}")
     acc, y = _run_dense(spl, Xq, sx, np.where(mask.astype(bool), Wq, np.int8(0)), sw)
     _assert_equal(acc, acc_ref, f"dense acc N={N} K={K} M={M}")
     _assert_equal(y, y_ref, f"dense Y N={N} K={K} M={M}")
@@ -247,9 +279,10 @@ def test_int8_prefill_llama_shapes_sampled(orc, spl, name, M, s):
     Xq, sx = synth.int8_activations(synth.activation_seed(j), M, K)
     rows = _sample_rows(M, N + M)
     acc_ref, y_ref = orc.linear_i8(Xq[rows], sx[rows], orc.pack(Wq, "i8", mask), sw)
-    acc, y = _run_sparse(spl, Xq, sx, Wq, mask, sw)
-    _assert_equal(acc[rows], acc_ref, f"{name} acc M={M}")
-    _assert_equal(y[rows], y_ref, f"{name} Y M={M}")
+    for run in (_run_plain, _run_sparse):
+        acc, y = run(spl, Xq, sx, Wq, mask, sw)
+        _assert_equal(acc[rows], acc_ref, f"{name} acc M={M} {run.__name__}")
+        _assert_equal(y[rows], y_ref, f"{name} Y M={M} {run.__name__}")
 
 
 def test_dense_int8_prefill(orc, spl):
@@ -321,6 +354,29 @@ def test_int8_expanded_and_dense_llama_rows(orc, spl, name):
     dacc, dy = _run_dense(spl, Xq, sx, Wm, sw)
     _assert_equal(dacc[rows], acc_ref, f"{name} dense acc")
     _assert_equal(dy[rows], y_ref, f"{name} dense Y")
+
+
+@pytest.mark.parametrize("M,K", [(70, (1 << 25) + 16), (16, (1 << 27) + 16)])
+def test_int8_activations_past_one_launch(spl, M, K):
+    """Activations past a launch's 32-bit addressing are taken some rows at a time (63 + 7, 15 + 1): codes of -1, 0
+    and 1, so that sums in float64 are exact."""
+    import torch
+
+    g = torch.Generator(device="cuda").manual_seed(K)
+    W = torch.randint(-1, 2, (3, K), generator=g, device="cuda", dtype=torch.int8)
+    mask = torch.randint(0, 16, (3, K), generator=g, device="cuda", dtype=torch.uint8) == 0
+    X = torch.randint(-1, 2, (M, K), generator=g, device="cuda", dtype=torch.int8)
+    Wc = spl.pack_sparse(W, mask.to(torch.uint8))
+    sx, sw = torch.rand(M, generator=g, device="cuda") + 0.5, torch.rand(3, generator=g, device="cuda") * 1e-3
+    ref = torch.zeros((M, 3), dtype=torch.float64, device="cuda")
+    for k in range(0, K, 1 << 23):
+        ref += X[:, k:k + (1 << 23)].double() @ (W * mask)[:, k:k + (1 << 23)].double().t().contiguous()
+    acc = torch.full((M + 1, 3), 77, dtype=torch.int32, device="cuda")
+    Y = torch.full((M + 1, 3), 7.0, dtype=torch.float16, device="cuda")
+    spl.sparse_linear_int8(X, sx, Wc, sw, out=Y[:M], acc_out=acc[:M])
+    assert torch.equal(acc[:M].double(), ref)
+    assert torch.equal(Y[:M], ((acc[:M].float() * sx[:, None]) * sw[None, :]).half())
+    assert (acc[M] == 77).all() and (Y[M] == 7.0).all(), "written past the outputs"
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])

@@ -1,14 +1,13 @@
-"""Host-side replay of the sparse int8 kernel's indexing (no GPU).
+"""Host-side replay of the streaming kernel's int8 form (k_wide.hip; no GPU).
 
-The int8 kernel multiplies pairs of 16 x 32 tiles (one v_mfma_i32_16x16x64_i8
-each), so its wave ranges and chunks keep pairs whole.  This test replays the
-schedule with the constants read from the kernel source and the tile offsets
-of real encodings from the oracle, and checks that every tile is multiplied
-once, that chunks end on a pair boundary unless the range ends there, and
-that every value piece, LDS window and staged activation read lies inside
-its buffer.  It also replays a lane's four nibble windows (aligned dword pair
-+ v_alignbyte_b32 + the selector table + v_perm_b32) and compares the
-expanded operand with the dense int8 row."""
+It multiplies pairs of 16 x 32 tiles (one v_mfma_i32_16x16x64_i8 each) in
+chunks of four tiles, whose slot holds them even when they are full.  This test
+replays the schedule with the constants read from the kernel source and the
+tile offsets of real encodings from the oracle, and checks that every tile is
+multiplied once, that chunks start at multiples of four, and that every value
+piece, LDS window and offsets lane lies inside its buffer.  It also replays a
+lane's four nibble windows (aligned dword pair + v_alignbyte_b32 + the selector
+table + v_perm_b32) and compares the expanded operand with the dense int8 row."""
 import os
 import re
 
@@ -18,91 +17,74 @@ import pytest
 import synth
 
 SRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
-                   "paper_2405_03594_amd", "csrc", "k_int8.hip")
+                   "paper_2405_03594_amd", "csrc", "k_wide.hip")
+TC = 4
 
 
-def _constants():
+def _slot():
     src = open(SRC).read()
-    chunk = int(re.search(r"constexpr int kI8Chunk = (\d+);", src).group(1))
-    vbuf = int(re.search(r"constexpr int kI8VBuf = (\d+);", src).group(1))
-    alloc = re.search(r"constexpr int kI8VBufAlloc = kI8VBuf \+ (\d+);", src)
-    assert alloc
-    for line in ("constexpr int C = MT == 4 ? kI8Chunk / 2 : kI8Chunk;",
-                 "const bool fit = lane >= r + 1 && lane <= r + jmax && (uint32_t)o <= lim;",
-                 "if (cn < jmax) cn &= ~1;",
-                 "const uint32_t lim = ch.a0 + kI8VBuf;",
-                 "const int t = base + lane < kend ? base + lane : kend;",
-                 "if (c1 - ob + C > kI8OffsetLanes) {",
-                 "return 64 * ((tile_steps(K) + 1) / 2) + 16;"):
+    for line in ("constexpr int TC = kQ ? 4 : 2;",
+                 "const int P = (S + TC - 1) / TC, L = (P + W - 1) / W;",
+                 "kbeg = TC * (wave * L < P ? wave * L : P);",
+                 "kend = kbeg + TC * L < S ? kbeg + TC * L : S;",
+                 "const int t = ob + lane < kend ? ob + lane : kend;",
+                 "if (c1 - ob + TC > kWave - 1) {",
+                 "a0[b] = (XB * o[0]) & ~15u;",
+                 "np[b] = (int)((XB * o[TC] - a0[b] + 15u) >> 4);",
+                 "if (np[b] > 2 * kWave && lane == 0)",
+                 "uint32_t p = before + t0 + ((t1 - t0) & (0u - (uint32_t)(fg >> 1)));"):
         assert line in src, f"kernel changed: update this replay ({line})"
-    return chunk, vbuf, vbuf + int(alloc.group(1))
+    m = re.search(r"constexpr int kWideSlot = (\d+) \+ (\d+);", src)
+    return int(m.group(1)) + int(m.group(2))
 
 
 def _ranges(S, W):
-    P = (S + 1) // 2
-    Lp = -(-P // W)
+    P = -(-S // TC)
+    L = -(-P // W)
     out = []
     for w in range(W):
-        pb = min(w * Lp, P)
-        pe = min(pb + Lp, P)
-        kbeg, kend = 2 * pb, min(2 * pe, S)
+        kbeg = TC * min(w * L, P)
+        kend = min(kbeg + TC * L, S)
         out.append((min(kbeg, kend), kend))
     return out
 
 
-def _chunks(tob, kbeg, kend, C, vbuf):
-    out, c0, ob = [], kbeg, kbeg
-    while c0 < kend:
-        if c0 - ob + C > 63:
+def _chunks(tob, kbeg, kend):
+    out, ob = [], kbeg
+    for c0 in range(kbeg, kend, TC):
+        if c0 > kbeg and c0 - ob + TC > 63:
             ob = c0
         window = [int(tob[min(ob + i, kend)]) for i in range(64)]
         r = c0 - ob
-        assert r + C <= 63
-        a0 = window[r] & ~15
-        lim = a0 + vbuf
-        jmax = min(C, kend - c0)
-        cn = sum(1 for i in range(64) if r + 1 <= i <= r + jmax and window[i] <= lim)
-        if cn < jmax:
-            cn &= ~1
-        assert cn >= 1
-        end = window[r + cn]
-        npieces = (end - a0 + 15) >> 4
-        out.append((c0, cn, a0, npieces, [window[r + j] for j in range(C + 1)]))
-        c0 += cn
+        assert r + TC <= 63
+        o = window[r:r + TC + 1]                          # tiles past the range: its end
+        a0 = o[0] & ~15
+        out.append((c0, a0, (o[TC] - a0 + 15) >> 4, o))
     return out
 
 
-@pytest.mark.parametrize("W", [8, 16])
-@pytest.mark.parametrize("MT", [1, 4])
+@pytest.mark.parametrize("W", [4, 8, 16])
 @pytest.mark.parametrize("N,K,s", [(16, 16, 0.5), (33, 48, 0.0), (20, 272, 0.7), (16, 4096, 0.0), (32, 4112, 0.7),
                                    (16, 11008, 0.5), (17, 512, 1.0), (16, 65552, 0.7)])
-def test_int8_schedule_stays_in_bounds(orc, N, K, s, MT, W):
-    chunk, vbuf, alloc = _constants()
-    C = chunk // 2 if MT == 4 else chunk
+def test_int8_schedule_stays_in_bounds(orc, N, K, s, W):
+    slot = _slot()
     Wq, mask, _ = synth.int8_weight(5 + N + K, N, K, s)
+    if s == 0.0:
+        mask[::16, 0] = 0                                 # full tiles off a 16-byte boundary
     T = orc.pack_tiled(Wq, "i8", mask)
     S, B = -(-K // 32), -(-N // 16)
     value_bytes = -(-T.nnz // 16) * 16 + 16
-    stride = 64 * ((S + 1) // 2) + 16
     for b in range(B):
         tob = T.tile_offsets[b * S:(b + 1) * S + 1]
         covered = np.zeros(S, dtype=np.int64)
         for kbeg, kend in _ranges(S, W):
-            assert kbeg % 2 == 0 or kbeg == kend          # empty ranges are clamped to the end
-            for c0, cn, a0, npieces, to in _chunks(tob, kbeg, kend, C, vbuf):
-                assert c0 % 2 == 0 and (cn % 2 == 0 or c0 + cn == kend), (c0, cn, kend)
-                covered[c0:c0 + cn] += 1
-                assert npieces <= vbuf // 16 and a0 + 16 * npieces <= value_bytes
-                for q in range(-(-cn // 2)):
-                    for tsel in (0, 1):
-                        j = 2 * q + tsel
-                        t0 = to[j]                       # j <= cn: at most the chunk's end offset
-                        assert t0 - a0 + 8 <= alloc       # a lane whose word is zero reads at its tile offset
-                        end_j = to[min(j + 1, cn)]
-                        assert end_j - a0 + 8 <= alloc    # the last nibble window of the tile
-                    for fg in range(4):                   # staged activation read of this pair
-                        kx = 64 * ((c0 >> 1) + q) + 16 * fg
-                        assert kx + 16 <= stride - 16
+            assert kbeg % TC == 0 or kbeg == kend         # empty ranges are clamped to the end
+            for c0, a0, pieces, o in _chunks(tob, kbeg, kend):
+                covered[c0:min(c0 + TC, kend)] += 1
+                assert pieces <= 129 and 16 * pieces <= slot
+                assert a0 + 16 * max(pieces, 1) <= value_bytes    # (lanes past the chunk read its first piece again)
+                for t in o:                               # a window starts at most at a tile's end, and reads 8 bytes
+                    assert ((t - a0) & ~3) + 8 <= slot
         assert (covered == 1).all()
 
 
@@ -130,7 +112,7 @@ def _perm(s0, s1, sel):
 
 @pytest.mark.parametrize("N,K,s", [(16, 16, 0.5), (20, 272, 0.7), (33, 96, 0.0), (17, 528, 0.9)])
 def test_int8_lane_expansion_matches_dense_rows(orc, N, K, s):
-    chunk, vbuf, alloc = _constants()
+    slot = _slot()
     Wq, mask, _ = synth.int8_weight(41 + N, N, K, s)
     T = orc.pack_tiled(Wq, "i8", mask)
     vals = np.concatenate([T.values.view(np.uint8), np.zeros(32, np.uint8)])
@@ -144,9 +126,10 @@ def test_int8_lane_expansion_matches_dense_rows(orc, N, K, s):
     for b in range(B):
         tob = T.tile_offsets[b * S:(b + 1) * S + 1]
         for kbeg, kend in _ranges(S, 8):
-            for c0, cn, a0, npieces, to in _chunks(tob, kbeg, kend, chunk, vbuf):
-                stage = np.zeros(alloc + 8, np.uint8)
+            for c0, a0, npieces, to in _chunks(tob, kbeg, kend):
+                stage = np.zeros(slot, np.uint8)
                 stage[:16 * npieces] = vals[a0:a0 + 16 * npieces]
+                cn = min(TC, kend - c0)
                 for q in range(-(-cn // 2)):
                     for lane in range(64):
                         fr, fg = lane & 15, lane >> 4
