@@ -5,9 +5,9 @@ Tolerance (fp16/bf16 outputs): |y - y64| <= max(2e-2, 1e-2 |y64|) per element:
 g and u are fp32 sums as in the plain linear layers, silu is evaluated in
 fp32 and the product is rounded once to the payload type.  Small shapes with
 ragged N, M and K are compared in full on both kernel families (the paired
-decode kernel for M <= 16 and the prefill tiling for any M); the Llama-2-7B
-gate/up shape is compared in full at decode batches and on sampled outputs at
-prefill batches."""
+decode kernel for M <= 16 and the prefill tiling for any M) and on what AUTO
+picks; the Llama-2-7B gate/up shape is compared in full at decode batches and
+on sampled outputs at prefill batches, each on the named family and on AUTO's."""
 import numpy as np
 import pytest
 
@@ -48,8 +48,9 @@ def test_gated_small(orc, spl, dtype, N, K, sg, su):
             Y = spl.sparse_linear_silu_mul(Xd[:M].contiguous(), g, u, algo=algo)
             assert_close(from_dev_f64(Y), ref[:M], f"{algo} {dtype} N={N} K={K} M={M}")
     for M in (17, 64, 129, 300):
-        Y = spl.sparse_linear_silu_mul(Xd[:M].contiguous(), g, u)
-        assert_close(from_dev_f64(Y), ref[:M], f"auto {dtype} N={N} K={K} M={M}")
+        for algo in ("auto", "prefill"):
+            Y = spl.sparse_linear_silu_mul(Xd[:M].contiguous(), g, u, algo=algo)
+            assert_close(from_dev_f64(Y), ref[:M], f"{algo} {dtype} N={N} K={K} M={M}")
 
 
 def test_gated_zero_matrices(orc, spl):
@@ -74,26 +75,32 @@ def test_gated_aligned_grids(orc, spl, N, K, M):
     prefill loads: 2N virtual rows on 128 x 256 and 64 x 128 tiles."""
     (g, u), (pg, pu) = _pair(spl, orc, 530 + N, N, K, "bf16", 0.7, 0.5)
     X = synth.activations(531, M, K, "bf16")
-    Y = spl.sparse_linear_silu_mul(to_dev(X, "bf16"), g, u)
-    assert_close(from_dev_f64(Y), orc.silu_mul_f64(X, pg, pu), f"N={N} K={K} M={M}")
+    ref = orc.silu_mul_f64(X, pg, pu)
+    for algo in ("prefill", "auto"):
+        Y = spl.sparse_linear_silu_mul(to_dev(X, "bf16"), g, u, algo=algo)
+        assert_close(from_dev_f64(Y), ref, f"{algo} N={N} K={K} M={M}")
 
 
 @pytest.mark.parametrize("s", [0.7, 0.5])
 def test_gated_llama_gate_up(orc, spl, s):
     """Llama-2-7B gate/up (11008 x 4096), the benchmark's batches: in full at
-    1, 4 and 16 (paired decode kernel), on sampled outputs at 512 and 2048
-    (prefill tiling)."""
+    1, 4 and 16 (paired decode kernel, and AUTO's), on sampled outputs at 512
+    and 2048 (prefill tiling, and AUTO's)."""
     N, K = 11008, 4096
     (g, u), (pg, pu) = _pair(spl, orc, synth.weight_seed(0, 4), N, K, "bf16", s, s)
     X = synth.activations(synth.activation_seed(4), 2048, K, "bf16")
     Xd = to_dev(X, "bf16")
     for M in (1, 4, 16):
-        Y = spl.sparse_linear_silu_mul(Xd[:M].contiguous(), g, u)
-        assert_close(from_dev_f64(Y), orc.silu_mul_f64(X[:M], pg, pu), f"gate/up M={M} s={s}")
+        ref = orc.silu_mul_f64(X[:M], pg, pu)
+        for algo in ("decode", "auto"):
+            Y = spl.sparse_linear_silu_mul(Xd[:M].contiguous(), g, u, algo=algo)
+            assert_close(from_dev_f64(Y), ref, f"gate/up {algo} M={M} s={s}")
     rng = np.random.default_rng(54)
     for M in (512, 2048):
         ms = np.concatenate([[0, M - 1, M // 2, 0], rng.integers(0, M, 3000)])
         ns = np.concatenate([[0, N - 1, 5000, 16], rng.integers(0, N, 3000)])
-        Y = from_dev_f64(spl.sparse_linear_silu_mul(Xd[:M].contiguous(), g, u))
-        assert_close(Y[ms, ns], orc.silu_mul_f64_pairs(X[:M], pg, pu, ms, ns), f"gate/up M={M} s={s}")
-        assert np.isfinite(Y).all()
+        ref = orc.silu_mul_f64_pairs(X[:M], pg, pu, ms, ns)
+        for algo in ("prefill", "auto"):
+            Y = from_dev_f64(spl.sparse_linear_silu_mul(Xd[:M].contiguous(), g, u, algo=algo))
+            assert_close(Y[ms, ns], ref, f"gate/up {algo} M={M} s={s}")
+            assert np.isfinite(Y).all()

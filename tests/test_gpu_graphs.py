@@ -183,18 +183,21 @@ def test_graph_replays_training_kernels_match_eager():
                        dtype=torch.uint8, device="cuda")
     ga, gb = torch.empty_like(A.values), torch.empty_like(Bm.values)
     dx = torch.empty((1024, K), dtype=torch.bfloat16, device="cuda")
-    dxs = torch.empty((40, 200), dtype=torch.bfloat16, device="cuda")
+    dxs, dxf = (torch.empty((40, 200), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    one = torch.empty((1,), dtype=torch.uint8, device="cuda")
 
     def run():
         spl.sparse_weight_grad_group([dYa, dYb], [X, X], [A, Bm], outs=[ga, gb])
-        spl.sparse_input_grad(dYd, A, out=dx)
+        spl.sparse_input_grad(dYd, A, out=dx, workspace=one)           # straight from W's tiles
         spl.sparse_input_grad(dYs, S, out=dxs, workspace=ws_s)
+        spl.sparse_input_grad(dYs, S, out=dxf)                         # scratch from the graph's pool
 
     def snapshot():
-        return [from_dev_bits(ga)[:A.nnz], from_dev_bits(gb)[:Bm.nnz], from_dev_bits(dx), from_dev_bits(dxs)]
+        return [from_dev_bits(ga)[:A.nnz], from_dev_bits(gb)[:Bm.nnz], from_dev_bits(dx), from_dev_bits(dxs),
+                from_dev_bits(dxf)]
 
     def poison():
-        for o in (ga, gb, dx, dxs):
+        for o in (ga, gb, dx, dxs, dxf):
             o.fill_(float("nan"))
         ws_s.fill_(0xCD)
 

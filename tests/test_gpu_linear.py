@@ -91,8 +91,9 @@ def test_decode_llama_shapes_bf16_70(orc, spl, name, N, K):
     ref = orc.linear_f64(X, ref_p)
     Xd = to_dev(X, "bf16")
     for M in (1, 4, 16):
-        Y = spl.sparse_linear(Xd[:M].contiguous(), Wc)
-        assert_close(from_dev_f64(Y), ref[:M], f"{name} M={M}")
+        for algo in ("decode", "auto"):
+            Y = spl.sparse_linear(Xd[:M].contiguous(), Wc, algo=algo)
+            assert_close(from_dev_f64(Y), ref[:M], f"{name} {algo} M={M}")
 
 
 def test_decode_cfg1_fp16_50(orc, spl):
@@ -186,8 +187,9 @@ def test_prefill_group(orc, spl):
         Ws.append(_pack(spl, W, mask, "bf16"))
         Xs.append(to_dev(X, "bf16"))
         refs.append(orc.linear_f64(X, orc.pack(W, "bf16", mask)))
-    for i, (Y, ref) in enumerate(zip(spl.sparse_linear_group(Xs, Ws), refs)):   # auto -> prefill at M = 70
-        assert_close(from_dev_f64(Y), ref, f"prefill group task {i}")
+    for algo in ("prefill", "auto"):                  # AUTO: the streaming kernel at M = 70
+        for i, (Y, ref) in enumerate(zip(spl.sparse_linear_group(Xs, Ws, algo=algo), refs)):
+            assert_close(from_dev_f64(Y), ref, f"{algo} group task {i}")
 
 
 @pytest.mark.parametrize("s", [0.7, 0.0])

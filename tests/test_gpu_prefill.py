@@ -93,10 +93,10 @@ def _sample_rows(M, seed, count=62):
 @pytest.mark.parametrize("name", [n for n, _, _ in synth.LLAMA2_7B_LINEARS])
 def test_prefill_llama_shapes_rows(orc, spl, name, s):
     """Every Llama-2-7B matrix at both sparsities and both prefill batches
-    (M = 512, 2048; the launch the auto choice takes): every output of 64
-    rows (the first, the last and 62 seeded ones) within the tolerance, and
-    the q matrix at M = 512 in full.  Rows are independent, so the oracle
-    runs on the sampled rows alone."""
+    (M = 512, 2048; expanded in place, and the launch the auto choice takes):
+    every output of 64 rows (the first, the last and 62 seeded ones) within the
+    tolerance, and the q matrix at M = 512 in full.  Rows are independent, so
+    the oracle runs on the sampled rows alone."""
     j = [n for n, _, _ in synth.LLAMA2_7B_LINEARS].index(name)
     _, N, K = synth.LLAMA2_7B_LINEARS[j]
     W, mask = synth.weight(synth.weight_seed(0, j), N, K, "bf16", s)
@@ -105,13 +105,12 @@ def test_prefill_llama_shapes_rows(orc, spl, name, s):
     Wc = _pack(spl, W, mask, "bf16")
     Xd = to_dev(X, "bf16")
     for M in (512, 2048):
-        Y = from_dev_f64(spl.sparse_linear(Xd[:M].contiguous(), Wc))
-        assert np.isfinite(Y).all()
-        if name == "q" and M == 512:
-            assert_close(Y, orc.linear_f64(X[:M], ref_p), f"{name} M={M} s={s} (all rows)")
-        else:
-            rows = _sample_rows(M, N + K + M)
-            assert_close(Y[rows], orc.linear_f64(X[rows], ref_p), f"{name} M={M} s={s} (64 rows)")
+        rows = np.arange(M) if name == "q" and M == 512 else _sample_rows(M, N + K + M)
+        ref = orc.linear_f64(X[rows], ref_p)
+        for algo in ("prefill", "auto"):
+            Y = from_dev_f64(spl.sparse_linear(Xd[:M].contiguous(), Wc, algo=algo))
+            assert np.isfinite(Y).all()
+            assert_close(Y[rows], ref, f"{name} {algo} M={M} s={s} ({len(rows)} rows)")
 
 
 def test_prefill_matches_decode_where_both_apply(orc, spl):

@@ -221,48 +221,57 @@ def test_weight_grad_llama_shapes(orc, spl, name, j, M):
                                      (128, 4096, 2048, 0.0)])
 def test_input_grad_from_packed_tiles(orc, spl, dtype, N, K, M, s):
     """dX = dY (W.Mask) straight from W's tiles (no packed transpose, no
-    workspace): shapes of one 128 x 256 block per CU over one, three, five
-    (an odd count: the two-stage loop's tail) and two 64-row stages of W,
-    every output compared with the oracle."""
+    workspace needed; one that is given keeps the call from the decoded
+    transpose): shapes of one 128 x 256 block per CU over one, three, five (an
+    odd count: the two-stage loop's tail) and two 64-row stages of W, every
+    output compared with the oracle, and the call without workspace too."""
     import torch
 
     W, mask = synth.weight(650 + N, N, K, dtype, s)
     dY = synth.activations(651 + M, M, N, dtype)
     Wc = spl.pack_sparse(to_dev(W, dtype), torch.from_numpy(mask).cuda())
     assert spl.lib().spl_sparse_input_grad_workspace_bytes(M, ctypes.byref(Wc.view())) == 0
-    dX = from_dev_f64(spl.sparse_input_grad(to_dev(dY, dtype), Wc))
-    assert_close(dX, orc.input_grad_f64(dY, dtype, orc.pack(W, dtype, mask)), f"dX {dtype} N={N} K={K} M={M}")
+    ref = orc.input_grad_f64(dY, dtype, orc.pack(W, dtype, mask))
+    for ws in (torch.empty((1,), dtype=torch.uint8, device="cuda"), None):
+        dX = from_dev_f64(spl.sparse_input_grad(to_dev(dY, dtype), Wc, workspace=ws))
+        assert_close(dX, ref, f"dX {dtype} N={N} K={K} M={M}")
 
 
 @pytest.mark.parametrize("N,K,M,s", [(104, 1000, 64, 0.7), (296, 264, 136, 0.5), (48, 520, 3, 0.9),
                                      (4096, 4096, 2000, 0.7)])
 def test_input_grad_decoded_fallback(orc, spl, N, K, M, s):
     """Shapes the direct kernel does not take: W decoded and transposed into
-    the workspace, then the dense product; compared with the oracle (every
-    output, or 64 full rows at 4096 x 4096, M = 2000)."""
+    the workspace that is given, then the dense product; without one, W's
+    decoded transpose in scratch.  Compared with the oracle (every output, or
+    64 full rows at 4096 x 4096, M = 2000)."""
     import torch
 
     W, mask = synth.weight(660 + N, N, K, "bf16", s)
     dY = synth.activations(661 + M, M, N, "bf16")
     Wc = spl.pack_sparse(to_dev(W, "bf16"), torch.from_numpy(mask).cuda())
-    assert spl.lib().spl_sparse_input_grad_workspace_bytes(M, ctypes.byref(Wc.view())) > 0
-    dX = from_dev_f64(spl.sparse_input_grad(to_dev(dY, "bf16"), Wc))
+    need = spl.lib().spl_sparse_input_grad_workspace_bytes(M, ctypes.byref(Wc.view()))
+    assert need > 0
+    ws = torch.empty((need,), dtype=torch.uint8, device="cuda")
+    dXs = [from_dev_f64(spl.sparse_input_grad(to_dev(dY, "bf16"), Wc, workspace=w)) for w in (ws, None)]
     rows = np.arange(M) if M * K <= 1 << 22 else np.sort(np.concatenate(
         [[0, M - 1], np.random.default_rng(N).choice(np.arange(1, M - 1), 62, replace=False)]))
     ref = orc.input_grad_f64(dY[rows], "bf16", orc.pack(W, "bf16", mask))
-    assert_close(dX[rows], ref, f"dX fallback N={N} K={K} M={M}")
+    for dX in dXs:
+        assert_close(dX[rows], ref, f"dX fallback N={N} K={K} M={M}")
 
 
 def test_input_grad_edge_cases(spl):
-    """No kept entry: dX = 0 on both paths; no tokens: nothing to do."""
+    """No kept entry: dX = 0 on every path; no tokens: nothing to do."""
     import torch
 
     for N, K, M in ((64, 8192, 1024), (40, 72, 24)):
         Wc = spl.pack_sparse(torch.zeros((N, K), dtype=torch.bfloat16, device="cuda"))
         assert Wc.nnz == 0
-        dX = spl.sparse_input_grad(torch.ones((M, N), dtype=torch.bfloat16, device="cuda"), Wc,
-                                   out=torch.full((M, K), 7.0, dtype=torch.bfloat16, device="cuda"))
-        assert not bool(dX.any())
+        need = max(spl.lib().spl_sparse_input_grad_workspace_bytes(M, ctypes.byref(Wc.view())), 1)
+        for ws in (torch.empty((need,), dtype=torch.uint8, device="cuda"), None):
+            dX = spl.sparse_input_grad(torch.ones((M, N), dtype=torch.bfloat16, device="cuda"), Wc, workspace=ws,
+                                       out=torch.full((M, K), 7.0, dtype=torch.bfloat16, device="cuda"))
+            assert not bool(dX.any())
     W, mask = synth.weight(670, 64, 128, "bf16", 0.5)
     Wc = spl.pack_sparse(to_dev(W, "bf16"), torch.from_numpy(mask).cuda())
     out = spl.sparse_input_grad(torch.empty((0, 64), dtype=torch.bfloat16, device="cuda"), Wc)
@@ -271,10 +280,10 @@ def test_input_grad_edge_cases(spl):
 
 @pytest.mark.parametrize("name,j", [("q", 0), ("gate", 4), ("down", 6)])
 def test_input_grad_llama_shapes(orc, spl, name, j):
-    """The bench's training shapes at M = 2048 (the direct kernel): 64 full
-    rows (0, M - 1 and 62 seeded) of dX against the oracle, and the same rows
-    through the packed transpose (spl_sparse_linear on Wt) within the same
-    tolerance."""
+    """The bench's training shapes at M = 2048 (the direct kernel, and the
+    decoded transpose): 64 full rows (0, M - 1 and 62 seeded) of dX against the
+    oracle, and the same rows through the packed transpose (spl_sparse_linear
+    on Wt) within the same tolerance."""
     import torch
 
     _, N, K = synth.LLAMA2_7B_LINEARS[j]
@@ -284,11 +293,14 @@ def test_input_grad_llama_shapes(orc, spl, name, j):
     md = torch.from_numpy(mask).cuda()
     Wc = spl.pack_sparse(to_dev(W, "bf16"), md)
     dYd = to_dev(dY, "bf16")
-    dX = from_dev_f64(spl.sparse_input_grad(dYd, Wc))
+    one = torch.empty((1,), dtype=torch.uint8, device="cuda")
+    assert spl.lib().spl_sparse_input_grad_workspace_bytes(M, ctypes.byref(Wc.view())) == 0
+    dXs = [from_dev_f64(spl.sparse_input_grad(dYd, Wc, workspace=ws)) for ws in (one, None)]
     rng = np.random.default_rng(j)
     rows = np.sort(np.concatenate([[0, M - 1], rng.choice(np.arange(1, M - 1), 62, replace=False)]))
     ref = orc.input_grad_f64(dY[rows], "bf16", orc.pack(W, "bf16", mask))
-    assert_close(dX[rows], ref, f"{name} dX M={M}")
+    for dX in dXs:
+        assert_close(dX[rows], ref, f"{name} dX M={M}")
     Wt = spl.pack_sparse(spl.transpose16(spl.unpack(Wc)), md.t().contiguous())
     dXt = from_dev_f64(spl.sparse_linear(dYd, Wt))
     assert_close(dXt[rows], ref, f"{name} dX via the packed transpose M={M}")
