@@ -587,7 +587,8 @@ double fg_decoded_us(const int64_t* N, int count, int64_t K, int64_t M, int64_t 
 // way by more than 10% twice.  Where it matters (in place / decoded): gate|up
 // gated at 129 rows 91 / 125 us, at 300 176 / 148, at 2048 530 / 395; 2 x 8192 x
 // 3072 gated at 512 rows 75 / 87, at 768 136 / 110; 2 x 13824 x 5120 at 256 rows
-// 164 / 215; 8192 x 1024 at 256 14 / 24; 4096 x 4096 at 129 44 / 39.
+// 164 / 215; 8192 x 1024 at 256 14 / 24; 4096 x 4096 at 129 44 / 39; 1536 x 1536
+// at 397 rows 19.4 / 16.7, at 640 18.6 / 19.5.
 bool fg_pays(const spl_matrix* const* W, int count, int64_t M, bool gated) {
   int64_t N[SPL_MAX_GROUP], bytes = 0, kmax = 0;
   double inplace = 0;
@@ -606,7 +607,11 @@ bool fg_pays(const spl_matrix* const* W, int count, int64_t M, bool gated) {
     N[0] *= 2, count = 1;
     inplace = fg_inplace_us(N[0], kmax, M);
   }
-  return inplace >= 16 && fg_decoded_us(N, count, kmax, M, bytes, gated) < inplace;
+  double decoded = fg_decoded_us(N, count, kmax, M, bytes, gated);
+  // one launch of tiles with K split: its activations and outputs are read and written meanwhile
+  if (count == 1 && !gated && ((N[0] + 63) / 64) * ((M + 127) / 128) <= device_cus())
+    decoded += 2.0 * M * (N[0] + kmax) / 3.5e6;
+  return inplace >= 16 && decoded < inplace;
 }
 
 template <class T, int kMode, bool kRagged>

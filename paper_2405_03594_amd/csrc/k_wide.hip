@@ -449,8 +449,10 @@ hipError_t wide_rows(WideGroupArg& g, hipStream_t s) {
 //     per CU: R 1, W 8 (4096 x 4096 at 64 rows 13.9; W 4 18.2); up to one block
 //     per CU in two splits: R 1, W 8 up to 48 rows each, else R 2, W 8
 //     (4096 x 11008 at 128 rows 38.9; R 1 54.4); below 3.5 per CU: R 1, W 4
-//     (q|k|v at 64 rows int8 19.6; W 8 25.9); above: R 2, W 4, three workgroups
-//     per CU (gate|up at 65 rows 62; R 2 W 8 85; at 33 rows 34.8; 44.9).
+//     (q|k|v at 64 rows int8 19.6; W 8 25.9; R 2 21.2); above, and for 57 to 64
+//     rows of 16-bit payloads from two per CU on (q|k|v 30.1; R 1 31.8; at 49
+//     30.0; 29.3): R 2, W 4, three workgroups per CU (gate|up at 65 rows 62; R 2
+//     W 8 85; at 33 rows 34.8; 44.9).
 template <class T>
 hipError_t wide_pick(WideGroupArg& g, hipStream_t s) {
   int64_t blocks = 0;
@@ -464,7 +466,8 @@ hipError_t wide_pick(WideGroupArg& g, hipStream_t s) {
   }
   if (blocks * splits <= cus || (blocks <= cus && rows <= 48)) return wide_rows<T, 1, 8, false, 1, 8>(g, s);
   if (blocks <= cus) return wide_rows<T, 2, 8, false, 1, 8>(g, s);
-  return 2 * blocks * splits < 7 * cus ? wide_rows<T, 1, 4, false, 6, 8>(g, s) : wide_rows<T, 2, 4, false, 6, 8>(g, s);
+  const bool pair = 2 * blocks * splits >= 7 * cus || (!wide_q<T>() && rows > 56 && blocks >= 2 * cus);
+  return pair ? wide_rows<T, 2, 4, false, 6, 8>(g, s) : wide_rows<T, 1, 4, false, 6, 8>(g, s);
 }
 
 // The gated half, by its pairs of row blocks: up to 32 rows W 16 up to one pair

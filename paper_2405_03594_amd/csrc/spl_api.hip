@@ -257,7 +257,7 @@ spl_status spl_sparse_linear_expanded(const void* X, int64_t M, const spl_matrix
 spl_status spl_sparse_linear_group(const spl_sparse_task* tasks, int32_t count, int64_t M, int32_t algo,
                                    hipStream_t stream) {
   if (!tasks || count < 1 || count > SPL_MAX_GROUP || M < 0) return SPL_ERR_INVALID_ARG;
-  int64_t blocks = 0;
+  int64_t blocks = 0, nnz = 0, elems = 0;
   int32_t resolved = algo;
   bool wide = algo == SPL_ALGO_AUTO && M > kStreamMaxM;
   for (int32_t i = 0; i < count; ++i) {
@@ -269,11 +269,13 @@ spl_status spl_sparse_linear_group(const spl_sparse_task* tasks, int32_t count, 
     resolved = a;                                      // (the launchers refuse a group that another task does not fit)
     wide = wide && spl::sparse_wide_fits(M, tasks[i].W->cols, 2);
     blocks += spl::tile_blocks(tasks[i].W->rows);
+    nnz += tasks[i].W->nnz, elems += tasks[i].W->rows * tasks[i].W->cols;
   }
   if (blocks >= kMaxDim) return SPL_ERR_OVERFLOW;
   if (M == 0) return SPL_OK;
   (void)hipGetLastError();
-  if (wide && !spl::few_rows_decode(M, blocks)) return launched(spl::launch_sparse_wide(tasks, count, M, stream));
+  if (wide && !spl::few_rows_decode(M, blocks, nnz, elems))
+    return launched(spl::launch_sparse_wide(tasks, count, M, stream));
   if (algo == SPL_ALGO_AUTO && M <= kStreamMaxM && resolved == SPL_ALGO_DECODE)
     return launched(spl::launch_sparse_row(tasks, count, stream));
   if (resolved == SPL_ALGO_DECODE) return launched(spl::launch_sparse_decode(tasks, count, M, stream));

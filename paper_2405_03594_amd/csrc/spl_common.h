@@ -211,12 +211,13 @@ hipError_t launch_gated_row(const void* X, const spl_matrix& Wg, const spl_matri
 // the gated half of an MLP, int8 groups.
 constexpr int64_t kWideMaxM = 128;
 // Where the decode kernel, which stages so few rows' activations once per workgroup, is the faster one: 2 rows from
-// 2.5 row blocks per CU on, 3 rows from four on.  Launches in us at 70%, streaming / decode: 4096 x 4096 (1 per CU)
-// at 2 rows 7.2 / 7.3; 2 x 5632 x 2048 (2.75) 9.3 / 9.2; q|k|v (3) 14.8 / 14.4, at 3 rows 14.8 / 15.4; gate|up (5.4)
-// at 2 to 5 rows 23.9 / 22.1, 24.6 / 23.3, 24.7 / 24.7, 24.9 / 28.8 (at 50% 27.0 / 27.1, 27.1 / 27.8, 27.5 / 29.5).
-inline bool few_rows_decode(int64_t M, int64_t blocks) {
+// 2.5 row blocks per CU on, 3 rows from four on, where at most 40% of the `elems` entries are kept.  Launches in us at
+// 70% pruned, streaming / decode: 4096 x 4096 (1 per CU) at 2 rows 7.2 / 7.3; 2 x 5632 x 2048 (2.75) 9.3 / 9.2; q|k|v
+// (3) 14.8 / 14.4, at 3 rows 14.8 / 15.4; gate|up (5.4) at 2 to 5 rows 23.9 / 22.1, 24.6 / 23.3, 24.7 / 24.7, 24.9 /
+// 28.8.  At 50% q|k|v at 2 rows 15.9 / 16.4, gate|up at 2 and 3 27.0 / 27.1, 27.1 / 27.8.
+inline bool few_rows_decode(int64_t M, int64_t blocks, int64_t nnz, int64_t elems) {
   const int64_t cus = device_cus();
-  return (M == 2 && 2 * blocks >= 5 * cus) || (M == 3 && blocks >= 4 * cus);
+  return 5 * nnz <= 2 * elems && ((M == 2 && 2 * blocks >= 5 * cus) || (M == 3 && blocks >= 4 * cus));
 }
 bool sparse_wide_fits(int64_t M, int64_t K, int bytes);
 hipError_t launch_sparse_wide(const spl_sparse_task* tasks, int count, int64_t M, hipStream_t s);

@@ -618,6 +618,7 @@ def test_scratch_is_offered_where_decoding_first_is_faster(L):
     assert group(128, (4096, 4096)) == 0                        # the streaming kernel's
     assert group(129, (4096, 4096)) == frag(4096, 4096, 32)
     assert group(397, *[(4096, 4096)] * 3) == 3 * frag(4096, 4096, 32)
+    assert group(397, (1536, 1536)) > 0 and group(640, (1536, 1536)) == 0
     for m in (129, 512, 2048):
         assert group(m, (1024, 1024)) == group(m, (768, 768)) == 0
     assert group(256, (8192, 1024)) == 0
