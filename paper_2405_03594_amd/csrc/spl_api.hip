@@ -20,16 +20,19 @@ constexpr int64_t kGatedDecodeMaxM = 16;           // the paired decode kernel h
 constexpr int64_t kStreamMaxM = 1;
 constexpr int64_t kGatedWideMaxM = 112;
 
-// The gated half by the streaming kernel, but for two ranges.  9 to 16 rows of
-// up to 1024 columns, whose 16 waves have two chunks each: the decode kernel (2
-// x 3072 x 1024 at 16 rows, 70% / 50%, 6.1 / 6.6 us there, 5.7 / 6.8 here; 2 x
-// 2048 x 768 4.9, 4.6).  More than 64 rows, so two workgroups per pair, where the
-// in-place kernel's 64-row tiles fill the chip in one round: 2 x 8192 x 3072
-// (256 tiles) at 65 and 112 rows 37.6, 42.0, in place 36.5, 37.7; 2 x 6144 x
-// 3072 (192) 26.9, 31.0, in place 36.2, 37.4.
-bool gated_wide(int64_t M, int64_t N, int64_t K) {
+// The gated half by the streaming kernel, but for two ranges.  Up to 16 rows of
+// up to 1024 columns, whose 16 waves have two chunks each, with at most 40% of
+// the entries kept: the decode kernel (us streaming / decode at 2 and 16 rows,
+// 70% pruned, 2 x 1024 x 1024 5.4 / 5.1, 5.4 / 4.9; 2 x 2048 x 768 4.9 / 4.8, 4.9
+// / 4.6; 2 x 3072 x 1024 5.8 / 5.8, 6.1 / 5.7; at 50% 5.9 / 6.1, 5.9 / 5.9; 5.7
+// / 6.0, 5.6 / 5.9; 6.5 / 6.9, 6.7 / 6.7).  More than 64 rows, so two workgroups
+// per pair, where the in-place kernel's 64-row tiles fill the chip in one round:
+// 2 x 8192 x 3072 (256 tiles) at 65 and 112 rows 37.6, 42.0, in place 36.5, 37.7;
+// 2 x 6144 x 3072 (192) 26.9, 31.0, in place 36.2, 37.4.
+bool gated_wide(int64_t M, const spl_matrix& Wg, const spl_matrix& Wu) {
+  const int64_t N = Wg.rows, K = Wg.cols;
   if (M > kGatedWideMaxM || !spl::sparse_wide_fits(M, K, 2)) return false;
-  if (M >= 9 && M <= kGatedDecodeMaxM && K <= 1024) return false;
+  if (M <= kGatedDecodeMaxM && K <= 1024 && 5 * (Wg.nnz + Wu.nnz) <= 4 * N * K) return false;
   const int64_t tiles = (2 * N + 63) / 64, cus = spl::device_cus();
   return !(M > 64 && tiles <= cus && 8 * tiles >= 7 * cus);
 }
@@ -380,7 +383,7 @@ spl_status spl_sparse_linear_silu_mul(const void* X, int64_t M, const spl_matrix
   (void)hipGetLastError();
   if (algo == SPL_ALGO_AUTO && M <= kStreamMaxM && ag == SPL_ALGO_DECODE)
     return launched(spl::launch_gated_row(X, *Wgate, *Wup, Y, stream));
-  if (algo == SPL_ALGO_AUTO && gated_wide(M, Wgate->rows, Wgate->cols))
+  if (algo == SPL_ALGO_AUTO && gated_wide(M, *Wgate, *Wup))
     return launched(spl::launch_gated_wide(X, M, *Wgate, *Wup, Y, stream));
   if (ag == SPL_ALGO_DECODE) return launched(spl::launch_gated_decode(X, M, *Wgate, *Wup, Y, stream));
   return launched(spl::launch_gated_prefill(X, M, *Wgate, *Wup, Y, stream));

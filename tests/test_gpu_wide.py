@@ -92,11 +92,11 @@ def test_wide_group(orc, spl, M):
         assert (o[M] == 7.0).all(), f"task {i}: written past its output"
 
 
-# 1024 and 1032 columns: both sides of where 9 to 16 rows take the decode kernel; 7160 .. 8192 rows: of where more than
-# 64 rows are expanded in place
+# 1024 and 1032 columns, 55% and 70% pruned: both sides of where up to 16 rows take the decode kernel; 7160 .. 8192
+# rows: of where more than 64 rows are expanded in place
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("N,K,s", [(40, 72, 0.7), (100, 1000, 0.5), (8200, 96, 0.6),
-                                   (2100, 1096, 0.6), (4800, 1096, 0.6), (33, 1024, 0.7), (33, 1032, 0.7),
+                                   (2100, 1096, 0.6), (4800, 1096, 0.6), (33, 1024, 0.7), (33, 1024, 0.55), (33, 1032, 0.7),
                                    (7160, 72, 0.6), (7170, 72, 0.6), (8192, 72, 0.6)])
 def test_wide_gated(orc, spl, dtype, N, K, s):
     (Wg, mg), (Wu, mu) = (_weight(600 + i + N, N, K, dtype, s) for i in range(2))
@@ -120,7 +120,7 @@ def test_wide_int8(orc, spl, N, K, s):
     p = orc.pack(Wq, "i8", mask)
     Wc = _packed(spl, Wq, mask, "i8")
     Xd, sxd, swd = to_dev(Xq, "i8"), torch.from_numpy(sx).cuda(), torch.from_numpy(sw).cuda()
-    for M in (11, 12, 15, 16, 17, 24, 32, 33, 48, 64, 65, 127):
+    for M in (8, 9, 11, 12, 15, 16, 17, 24, 32, 33, 48, 64, 65, 127):
         acc_ref, y_ref = orc.linear_i8(Xq[:M], sx[:M], p, sw)
         acc = torch.empty((M, N), dtype=torch.int32, device="cuda")
         Y = spl.sparse_linear_int8(Xd[:M].contiguous(), sxd[:M].contiguous(), Wc, swd, acc_out=acc)
