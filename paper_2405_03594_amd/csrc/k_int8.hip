@@ -20,12 +20,13 @@ constexpr int64_t kI8MaxBytes = (int64_t)1 << 31;   // activations of one launch
 // Batches of more rows than one batch fragment go to the streaming kernel (q|k|v 12.4 us a launch at 17 rows, 13.8 at
 // 32, 25.4 at 127; gate|up 20.2, 21.3, 46.2).
 constexpr int64_t kI8WideMinM = 17;
-// On up to one row block per CU, where the four-tile kernel waits for its activations most, from 12 rows, or 16 past
-// 4096 columns: its launches / the streaming ones at 12, 14 and 16 rows 3072 x 3072 5.8 / 5.4, 5.9 / 5.4, 6.1 / 5.4
-// us, 4096 x 4096 6.2 / 6.2, 6.4 / 6.2, 6.6 / 6.2, 4096 x 11008 10.1 / 10.6, 10.4 / 10.7, 10.9 / 10.8; q|k|v, 3
-// blocks per CU, 10.9 / 11.2 at 12.
+// On up to one row block per CU, where the four-tile kernel waits for its activations most, from 9 rows of up to 3072
+// columns, 12 of up to 4096 and 16 past them: its launches / the streaming ones at 9, 12, 14 and 16 rows 3072 x 3072
+// 5.6 / 5.4, 5.8 / 5.4, 5.9 / 5.4, 6.1 / 5.4 us (at 8 rows, where only decoding waits, 5.3 to 5.6 / 5.2 to 5.5),
+// 4096 x 4096 6.0 / 6.2, 6.2 / 6.2, 6.4 / 6.2, 6.6 / 6.2, 4096 x 11008 at 12, 14 and 16 10.1 / 10.6, 10.4 / 10.7,
+// 10.9 / 10.8; 2048 x 2048 at 9 and 12 4.5 / 4.4, 4.65 / 4.4; q|k|v, 3 blocks per CU, 10.9 / 11.2 at 12.
 bool i8_wide_small(int64_t M, int64_t blocks, int64_t kmax) {
-  return M >= (kmax <= 4096 ? 12 : 16) && blocks <= device_cus();
+  return M >= (kmax <= 3072 ? 9 : kmax <= 4096 ? 12 : 16) && blocks <= device_cus();
 }
 
 __device__ __forceinline__ i32x4 mfma_i8(u32x4 a, u32x4 b, i32x4 c) {
