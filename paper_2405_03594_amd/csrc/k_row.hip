@@ -290,15 +290,17 @@ hipError_t row_launch(const RowGroupArg& g, hipStream_t s) {
 
 // Waves per workgroup.  Measured (us at 16 / 8 / 4 waves, bf16 at 70%): up to
 // one row block per CU 16 (4096 x 4096 6.3 / 7.2 / 9.1, 4096 x 11008 11.5 /
-// 14.9 / 19.2); up to four 8 (5120 x 5120, 1.25 per CU, of which only one fits
-// beside its 16 waves: 13.1 / 10.7 / 11.7; q|k|v 15.4 / 12.9 / 13.2); above, 4
-// (gate|up 26.2 / 19.9 / 19.3; 2 x 13824 x 5120 42.8 / 29.8 / 28.3), except the
-// gated pair, whose waves split twice the matrices (21.3 / 18.0 / 20.2).
+// 14.9 / 19.2); below 3.5 8 (5120 x 5120, 1.25 per CU, of which only one fits
+// beside its 16 waves: 13.1 / 10.7 / 11.7; q|k|v, 3 per CU, 15.4 / 12.9 / 13.2);
+// above, 4 (3 x 5120 x 5120, 3.75 per CU, 23.6 / 18.2 / 17.4, at 50% 26.2 / 24.2 /
+// 22.8; 2 x 8192 x 3072, 4 per CU, 17.2 / 13.3 / 12.5; gate|up 26.6 / 19.5 / 18.8;
+// 2 x 13824 x 5120 38.7 / 27.6 / 28.3), except the gated pair, whose waves split
+// twice the matrices (21.3 / 18.0 / 20.2).
 template <class T, bool kGated>
 hipError_t row_pick(const RowGroupArg& g, hipStream_t s) {
   const int64_t blocks = g.first[g.count], cus = device_cus();
   if (blocks <= cus) return row_launch<T, 16, kGated>(g, s);
-  return blocks < 4 * cus || kGated ? row_launch<T, 8, kGated>(g, s) : row_launch<T, 4, kGated>(g, s);
+  return 2 * blocks < 7 * cus || kGated ? row_launch<T, 8, kGated>(g, s) : row_launch<T, 4, kGated>(g, s);
 }
 
 // A row's activations, and a row block's words, are addressed with 32-bit byte offsets.
