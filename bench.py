@@ -99,13 +99,15 @@ def make_activations(dtype: str, mmax: int):
     return xs
 
 
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_sparse_decode_llama7b_stack_traffic.txt")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_2405_03594_amd", "csrc", f) for f in ("k_decode.hip", "spl_common.h")]
+DECODE_KERNELS = "k_sparse_row, k_sparse_decode, k_sparse_wide"    # what AUTO launches at batches 1..32
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sparse_decode_llama7b_layer_traffic.txt")
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2405_03594_amd", "csrc", f)
+                  for f in ("k_row.hip", "k_decode.hip", "k_wide.hip", "spl_common.h")]
 
 
 def measured_traffic():
-    """HBM bytes per launch of the sparse decode kernel from the committed
-    rocprofv3 FETCH_SIZE / WRITE_SIZE summary, or None when the kernel source
+    """HBM bytes per launch of the sparse decode kernels from the committed
+    rocprofv3 FETCH_SIZE / WRITE_SIZE summary, or None when a kernel source
     has changed since the counters were taken (or there is no summary)."""
     import hashlib
 
@@ -296,7 +298,7 @@ def run_single(args):
                  f"{copies * 2 * N * K / 1e9:.2f} GB dense); a step is one graph of {copies} back-to-back "
                  f"products, one per copy",
                  {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                  "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "k_sparse_decode",
+                  "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "k_sparse_row",
                   "bytes_per_launch": int(nbytes), "avg_launch_us": round(sp_gpu * 1e3, 3)},
                  cpu, {"gpu_us": round(sp_gpu * 1e3, 3), "dense_gpu_us": round(dn_gpu * 1e3, 3),
                        "speedup_vs_dense": round(dn_gpu / sp_gpu, 3)}, dtype="f16")
@@ -489,7 +491,7 @@ def run_int8(args):
                  "(per-row scales) and int8 activations (per-token scales), 70% sparsity, batches 1, 16, 64, "
                  "4 layers rotated",
                  {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                  "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "k_sparse_int8",
+                  "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "k_int8_quad, k_sparse_wide<int8>",
                   "bytes_per_launch": int(step_bytes / len(units)), "avg_launch_us": round(launch_ms * 1e3, 3)},
                  cpu, {"per_M": per_M}, dtype="i8")
 
@@ -605,7 +607,7 @@ def run_int8_prefill(args):
                  f"magnitude sparsity, prefill M = 512 and 2048",
                  {"bound": "mfma", "achieved": round(achieved, 1), "peak": MFMA_I8_PEAK_TOPS, "unit": "TOP/s",
                   "frac": round(achieved / MFMA_I8_PEAK_TOPS, 4), "traffic": None,
-                  "kernel": "k_sparse_prefill<int8>", "ops_per_launch": "dense-equivalent 2*M*N*K",
+                  "kernel": "k_frag_expand8 + k_frag_gemm<int8>", "ops_per_launch": "dense-equivalent 2*M*N*K",
                   "avg_launch_us": round(launch_ms * 1e3, 3)},
                  cpu, {"per_M": per_M, "sparsity": args.sparsity}, dtype="i8")
 
@@ -695,7 +697,7 @@ def run_gated(args):
                  f"{ncopy} device copies ({ncopy * pair_bytes / 1e9:.2f} GB packed), a step is one graph of "
                  f"{len(units)} launches (every copy at every batch)",
                  {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                  "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "k_sparse_decode2<gated>",
+                  "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "k_sparse_row<gated>, k_sparse_wide<gated>",
                   "bytes_per_launch": int(sum(nbytes.values()) / len(Ms)), "avg_launch_us": round(launch_ms * 1e3, 3)},
                  cpu, {"per_M": per_M, "sparsity": args.sparsity})
 
@@ -937,7 +939,7 @@ def run_int4(args):
                  "Llama-2-7B decoder layer, 7 linears, 4-bit weights (per-row scales) and int8 activations "
                  "(per-token scales), 70% sparsity, batches 1 and 16, one launch per matrix, 4 layers rotated",
                  {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                  "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "k_sparse_i4",
+                  "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "k_int4_quad",
                   "bytes_per_launch": int(sum(nbytes(*u) for u in units) / len(units)),
                   "avg_launch_us": round(launch_ms * 1e3, 3)},
                  cpu, {"per_M": per_M}, dtype="i8")
@@ -1132,7 +1134,7 @@ def run_stack(args):
                 "4096x11008), distinct seeds, bf16, 70% unstructured magnitude sparsity in bitmask format; one step "
                 f"= the stack at decode batches {Ms} ({sum(Ms)} tokens), 4 dependent launches per layer",
                 {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic(), "kernel": "k_sparse_decode",
+                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic(), "kernel": DECODE_KERNELS,
                  "bytes_per_launch": int(bytes_per_launch), "avg_launch_us": round(avg_launch_ms * 1e3, 3),
                  "peak_measured": round(probe, 1), "frac_of_measured": round(achieved / probe, 4)},
                 cpu,
@@ -1175,7 +1177,7 @@ def run_stack_layer(args):
                  "Llama-2-7B linear stack, 32 layers x 7 matrices, bf16, 70%; one launch per layer (its seven "
                  f"independent matrices), decode batches {Ms}",
                  {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                  "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "k_sparse_decode",
+                  "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "kernel": DECODE_KERNELS,
                   "bytes_per_launch": int(bpl), "avg_launch_us": round(avg_launch_ms * 1e3, 3)},
                  None, {"per_M": per_M})
 
@@ -1333,7 +1335,7 @@ def main():
             "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": None,                      # the committed counters cover the stack's launch mix
-            "kernel": "k_sparse_decode",
+            "kernel": DECODE_KERNELS,
             "bytes_per_launch": int(bytes_per_launch),
             "avg_launch_us": round(launch_ms * 1e3, 3),
         },

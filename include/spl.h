@@ -86,11 +86,14 @@ typedef enum {
 typedef enum { SPL_F16 = 1, SPL_BF16 = 2, SPL_I8 = 3, SPL_I4 = 4 } spl_dtype;
 
 /* Kernel family for spl_sparse_linear_ex / spl_dense_linear_ex.
- * AUTO picks by batch size M: DECODE for one row, a streaming kernel with up
- * to four batch fragments per expanded tile for 2 <= M <= 128 (the gated half:
- * M <= 112, and from one row on), then PREFILL.  DECODE is the small-batch
- * kernel (M <= 32): compressed rows are decompressed into MFMA operand tiles
- * with the batch padded to 16 or 32.  PREFILL is the large-batch tiled kernel:
+ * AUTO picks by batch size M, and between kernels of one size by the matrices'
+ * shapes and kept share: a kernel of its own for one row; for 2 <= M <= 128
+ * (the gated half: M <= 112) a streaming kernel with up to four batch fragments
+ * per expanded tile, but DECODE where that is the faster one (2 or 3 rows of
+ * large groups; the gated half's narrow matrices up to 16 rows) and, for the
+ * gated half, PREFILL where its tiles fill the chip in one round; then PREFILL.
+ * DECODE is the small-batch kernel (M <= 32): compressed rows are decompressed
+ * into MFMA operand tiles with the batch padded to 16 or 32.  PREFILL is the large-batch tiled kernel:
  * compressed tiles are decompressed into LDS and feed bf16/fp16 MFMA (any M). */
 typedef enum { SPL_ALGO_AUTO = 0, SPL_ALGO_DECODE = 1, SPL_ALGO_PREFILL = 2 } spl_algo;
 
@@ -210,9 +213,9 @@ spl_status spl_sparse_linear(const void* X, int64_t M, const spl_matrix* Wc, voi
 
 /* As spl_sparse_linear with an explicit kernel family (spl_algo).
  * DECODE requires M <= 32 and 2 M K <= 2^31 (the activations addressed with
- * 32-bit byte offsets); SPL_ERR_UNSUPPORTED otherwise, and AUTO then picks
- * PREFILL.  AUTO's streaming kernel needs 2 min(M, 64) K <= 2^31; beyond that
- * AUTO picks DECODE or PREFILL as above. */
+ * 32-bit byte offsets); SPL_ERR_UNSUPPORTED otherwise.  AUTO takes a kernel
+ * that can address the activations: the one-row kernel needs K <= 2^30, the
+ * streaming kernel 2 min(M, 64) K <= 2^31; past that it is PREFILL. */
 spl_status spl_sparse_linear_ex(const void* X, int64_t M, const spl_matrix* Wc, void* Y, int32_t algo,
                                 hipStream_t stream);
 
@@ -353,9 +356,8 @@ spl_status spl_magnitude_mask_noalloc(const void* W, int32_t dtype, int64_t N, i
  *   the result to the payload type.  One launch, no intermediate in memory.
  *   Wgate, Wup  views in the tile layout with the same dtype, rows (N) and cols (K).
  *   X, Y        as in spl_sparse_linear (Y [M][N]).
- *   algo        SPL_ALGO_AUTO (the streaming kernel for M <= 112, else
- *               PREFILL), DECODE (M <= 16, SPL_ERR_UNSUPPORTED otherwise) or
- *               PREFILL (any M).
+ *   algo        SPL_ALGO_AUTO (see spl_algo), DECODE (M <= 16,
+ *               SPL_ERR_UNSUPPORTED otherwise) or PREFILL (any M).
  * Errors as spl_sparse_linear; mismatched dtypes or shapes -> SPL_ERR_INVALID_ARG. */
 spl_status spl_sparse_linear_silu_mul(const void* X, int64_t M, const spl_matrix* Wgate, const spl_matrix* Wup,
                                       void* Y, int32_t algo, hipStream_t stream);

@@ -360,7 +360,11 @@ def unpack(Wc: SparseMatrix, out: torch.Tensor | None = None, stream=None) -> to
 
 def sparse_linear(X: torch.Tensor, Wc: SparseMatrix, out: torch.Tensor | None = None, algo: str = "auto",
                   stream=None) -> torch.Tensor:
-    """Y [M][N] = X [M][K] (W . Mask)^T, fp32 accumulation, output in X's dtype."""
+    """Y [M][N] = X [M][K] (W . Mask)^T, fp32 accumulation, output in X's dtype.
+
+    Above 128 rows algo="auto" may multiply through a decoded copy of W: 2 bytes an entry from the caching allocator,
+    for the call (a captured graph's pool keeps them), also where `out` is given.  Without the memory, or with
+    algo="prefill", the tiles are expanded in place."""
     L = lib()
     M = _rows_of(X, "X")
     _arg(X, "X", shape=(M, Wc.cols), dtype=Wc.dtype, device=False)
@@ -413,7 +417,8 @@ def sparse_linear_expanded(X: torch.Tensor, Wc: SparseMatrix, out: torch.Tensor 
 def sparse_linear_silu_mul(X: torch.Tensor, Wgate: SparseMatrix, Wup: SparseMatrix, out: torch.Tensor | None = None,
                            algo: str = "auto", stream=None) -> torch.Tensor:
     """Y [M][N] = silu(X Wgate^T) * (X Wup^T): the gated half of a Llama MLP in
-    one launch (see spl_sparse_linear_silu_mul)."""
+    one launch (see spl_sparse_linear_silu_mul).  Above 112 rows algo="auto" may take memory for a decoded copy of
+    both matrices as in sparse_linear."""
     L = lib()
     if (Wup.rows, Wup.cols, Wup.dtype) != (Wgate.rows, Wgate.cols, Wgate.dtype):
         raise ValueError("gate and up must share shape and dtype")
@@ -571,7 +576,9 @@ def sparse_weight_grad_group(dYs, Xs, mats, outs=None, workspace: torch.Tensor |
 
 def sparse_input_grad(dY: torch.Tensor, Wc: SparseMatrix, out: torch.Tensor | None = None,
                       workspace: torch.Tensor | None = None, stream=None) -> torch.Tensor:
-    """dX [M][K] = dY [M][N] (W . Mask) from W's packed tiles (see spl_sparse_input_grad)."""
+    """dX [M][K] = dY [M][N] (W . Mask) from W's packed tiles (see spl_sparse_input_grad).  Without a `workspace`, and
+    where it is the faster way, through W's decoded transpose: 2 bytes an entry from the caching allocator, for the
+    call (a captured graph's pool keeps them)."""
     L = lib()
     M = _rows_of(dY, "dY")
     _arg(dY, "dY", shape=(M, Wc.rows), dtype=Wc.dtype, device=False)
@@ -690,7 +697,10 @@ def quantize_rows_i8(X: torch.Tensor, out: torch.Tensor | None = None, scales: t
 def sparse_linear_int8(Xq: torch.Tensor, x_scales: torch.Tensor, Wqc: SparseMatrix, w_scales: torch.Tensor,
                        out: torch.Tensor | None = None, acc_out: torch.Tensor | None = None,
                        stream=None) -> torch.Tensor:
-    """fp16 Y = dequant(int32 Xq (Wq . Mask)^T) with per-token and per-channel scales."""
+    """fp16 Y = dequant(int32 Xq (Wq . Mask)^T) with per-token and per-channel scales.
+
+    From 128 rows on most matrices are multiplied through a decoded copy: 1 byte an entry from the caching allocator,
+    for the call (a captured graph's pool keeps them).  Without the memory the tiles are expanded in place."""
     L = lib()
     M = _rows_of(Xq, "Xq")
     _q_args(Xq, x_scales, Wqc.rows, Wqc.cols, w_scales, M, device=False)
@@ -785,7 +795,8 @@ def dense_linear_int8(Xq: torch.Tensor, x_scales: torch.Tensor, Wq: torch.Tensor
 
 def sparse_linear_group(Xs, Wcs, outs=None, algo: str = "auto", stream=None):
     """Y_i = X_i (W_i . Mask_i)^T for up to MAX_GROUP independent layers sharing the
-    batch size and dtype, in one launch (decode) or one launch per layer (prefill)."""
+    batch size and dtype, in one launch (decode) or one launch per layer (prefill).  Above
+    128 rows algo="auto" may take memory for decoded copies of all of them, as in sparse_linear."""
     L = lib()
     n = len(Xs)
     if n != len(Wcs) or not 1 <= n <= MAX_GROUP:
@@ -848,7 +859,8 @@ def dense_linear_group(Xs, Ws, outs=None, algo: str = "auto", stream=None):
 
 def sparse_linear_int8_group(Xqs, x_scales, Wqcs, w_scales, outs=None, acc_outs=None, stream=None):
     """fp16 Y_i = dequant(int32 Xq_i (Wq_i . Mask_i)^T) for up to MAX_GROUP independent
-    int8 layers sharing the batch size, in one launch."""
+    int8 layers sharing the batch size, in one launch; from 128 rows on through decoded
+    copies of all of them, as in sparse_linear_int8."""
     L = lib()
     n = len(Xqs)
     if not (n == len(x_scales) == len(Wqcs) == len(w_scales)) or not 1 <= n <= MAX_GROUP:

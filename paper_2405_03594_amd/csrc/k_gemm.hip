@@ -28,10 +28,12 @@
 // accumulators between registers every iteration (4096 x 4096 x 2048 tokens:
 // 74.5 us; without 59.6).
 //
-// Measured on one Llama-2-7B layer, bf16, 70%, against the tiled kernels that
-// expand in place: 2048 tokens q|k|v 283 -> 35 + 179 us (decoding + product,
-// 1149 TFLOP/s), gate|up 529 -> 44 + 333, down 233 -> 23 + 141 (1311 TFLOP/s);
-// 397 tokens q|k|v 137 -> 35 + 54, gate|up 186 -> 44 + 84, down 116 -> 23 + 53.
+// Measured on one Llama-2-7B layer, bf16, 70%, cold weights, against the tiled
+// kernels that expand in place: 2048 tokens q|k|v 275 -> 39 + 183 us (decoding +
+// product, 1126 TFLOP/s), o 87 -> 15 + 69, gated gate|up 530 -> 67 + 350 (1055),
+// down 231 -> 36 + 172 (1074), so 157 us of a layer are decoding, in int8 90;
+// 397 tokens, both together: q|k|v 130 -> 89, o 44 -> 37, gate|up 182 -> 150,
+// down 109 -> 87.
 #include <type_traits>
 
 #include "spl_common.h"
@@ -338,9 +340,11 @@ __device__ __forceinline__ u32x4 fg_place(uint32_t byte, u32x2 v0, u32x2 v1, con
 }
 
 // 16-bit payloads: fragment (row block b, step s) is tile (b, s); steps past S
-// are zeros.  HBM bound: each value read once, 1 KB written per tile with one
-// coalesced store (gate: 22 us for 32 MB + 90 MB).  The windows read at most
-// 16 bytes past the last payload, which every values buffer has.
+// are zeros.  Each value is read once, 1 KB written per tile with one coalesced
+// store; bound by a wave's two dependent trips (offsets and words, then values)
+// with four fragments in flight rather than by HBM (gate|up 67 us for 66 MB
+// read and 180 MB written, 3.7 TB/s, where plain reads reach 6.5).  The windows
+// read at most 16 bytes past the last payload, which every values buffer has.
 __global__ void __launch_bounds__(256) k_frag_expand16(const FgExpandArg g) {
   __shared__ u32x2 lut[16];
   if (threadIdx.x < 16) lut[threadIdx.x] = u32x2{nibble_selector16(threadIdx.x, 0), nibble_selector16(threadIdx.x, 1)};
@@ -537,7 +541,13 @@ hipError_t fg_launch(FgGroupArg& g, hipStream_t s) {
 // 62 for both; of 64 x 128, four per CU, 24, 42, 60 and 78.  So gate|up at
 // 2048 tokens (1376 / 2752 / 5504 tiles) takes 128 x 128 (333 us; 340 with
 // 128 x 256), q|k|v there 128 x 256 (179; 185), q at 512 tokens 64 x 128
-// (24.5; 31 and 50 with the larger ones).
+// (24.5; 31 and 50 with the larger ones).  A stage is as many MFMA cycles in
+// fp16, and in int8, where it holds 128 columns.  Over 68 launches of 8 sets of
+// widths at 256 to 2048 rows in fp16, int8 and the gated form, each forced to
+// all three tiles, the choice is within 5% of the best but for seven: gate|up
+// fp16 at 2048 rows 403 us, 375 with 128 x 256; gated at 256, which is expanded
+// in place; 2 x 5632 x 2048 at 2048 rows int8 70, gated 115, 64 and 105 with 128
+// x 128; and int8 at 512 to 2048 rows on three widths by 5 to 7%.
 enum { kFgL, kFgM, kFgS };
 struct FgCost {
   int tile;
@@ -623,7 +633,8 @@ hipError_t fg_product_r(FgGroupArg& g, hipStream_t s) {
       // (eight waves for int8, whose MFMAs the compiler keeps off the accumulation registers)
       if constexpr (!kRagged && fg_q<T>()) return fg_launch<T, 4, 4, 2, 4, kMode, kRagged>(g, s);
       else if constexpr (!kRagged) return fg_launch<T, 4, 8, 2, 2, kMode, kRagged>(g, s);
-      // (with the ragged columns' selects the large tile loses its lead)
+      // (ragged columns have no large tile, which would give 0 to 5%: 3 x 3000 x 3000 at 2048 rows 142 us, 141 with
+      // it; 2 x 8008 x 3000 246, 239; 2 x 8008 x 4072 320, 304)
     case kFgM: return fg_launch<T, 4, 4, 2, 2, kMode, kRagged>(g, s);
     default: return fg_launch<T, 2, 4, 2, 2, kMode, kRagged>(g, s);
   }

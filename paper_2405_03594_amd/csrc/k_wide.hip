@@ -22,10 +22,10 @@
 //     touches a different cache line in each lane, one lane per cycle of the
 //     address unit (counters of a version that loaded operands directly: 67
 //     cache accesses per instruction, 16 bytes per cycle and CU, the unit busy
-//     two thirds of a 4096 x 4096 launch at 64 rows).  Eight lanes read one
+//     two thirds of a 4096 x 4096 launch at 64 rows, 19.8 us).  Eight lanes read one
 //     row's 128 bytes instead, 64 bytes per cycle; LDS (pieces swizzled by
-//     row) turns them.  4096 x 4096 at 64 rows: 19.8 -> 14.7 us; gate|up at 16
-//     rows 30.5 us in the paired decode kernel -> 23.9 us;
+//     row) turns them: 13.9 us there, and gate|up at 16 rows 26 us (30.5 in the
+//     paired decode kernel);
 //   * the waves' partial sums are added in LDS in wave order and rounded once
 //     (int8: exact sums and the int8 path's epilogue).
 //

@@ -16,7 +16,11 @@ constexpr int64_t kDecodeMaxM = 32;
 constexpr int64_t kGatedDecodeMaxM = 16;           // the paired decode kernel holds one 16-row batch tile
 // AUTO: the one-row kernel up to this many rows, then the streaming kernel of
 // several batch fragments as far as it goes (spl::kWideMaxM; the gated half:
-// kGatedWideMaxM), then the prefill kernels.
+// kGatedWideMaxM) but for few_rows_decode's and gated_wide's exceptions, then
+// the prefill kernels.  At 112 / 128 gated rows streaming / the kernels after
+// it: 2 x 4096 x 4096 29.9 / 42.9 us, 30.0 / 42.9; gate|up 70.7 / 79.0, 71.3 /
+// 75.7; so the line is below where they meet (past 128: 2 x 4096 x 4096 at 192
+// rows 38.3 / 45.2, gate|up 101.4 / 98.4).
 constexpr int64_t kStreamMaxM = 1;
 constexpr int64_t kGatedWideMaxM = 112;
 

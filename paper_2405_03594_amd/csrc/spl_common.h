@@ -209,6 +209,10 @@ hipError_t launch_gated_row(const void* X, const spl_matrix& Wg, const spl_matri
 // Streaming kernel for batches of up to kWideMaxM rows whose activations
 // (`bytes` each) it can address: groups of 1..SPL_MAX_GROUP validated tasks,
 // the gated half of an MLP, int8 groups.
+// Two workgroups of 64 rows per row block: at 128 rows, streaming / in place, 4096 x 4096 18.0 / 45.9 us, 4096 x 11008
+// 39.3 / 114.6, q|k|v 40.9 / 137.6, gate|up 73.0 / 93.2.  With a third and a fourth it was, against decoding into
+// scratch, 32.7 / 38.4, 74 / 85, 60 / 69, 102 / 120 at 192 rows but 33 / 38, 75 / 86, 70 / 70, 125 / 117 at 256, where
+// 8192 x 1024 takes 18.8 / 14.4: the line is below where they meet, which the shape decides.
 constexpr int64_t kWideMaxM = 128;
 // Where the decode kernel, which stages so few rows' activations once per workgroup, is the faster one: 2 rows from
 // 2.5 row blocks per CU on, 3 rows from four on, where at most 40% of the `elems` entries are kept.  Launches in us at
@@ -225,7 +229,11 @@ hipError_t launch_gated_wide(const void* X, int64_t M, const spl_matrix& Wg, con
                              hipStream_t s);
 hipError_t launch_int8_wide(const spl_int8_task* tasks, int count, int64_t M, hipStream_t s);
 // int8 batches from this size on use the MFMA-tiled kernels (or, with scratch,
-// the decoded product) instead of the streaming ones.
+// the decoded product) instead of the streaming ones, the dense comparator's
+// too.  The last streaming launches / the first decoded ones, 127 / 128 rows:
+// 4096 x 4096 12.4 / 27.2 us, q|k|v 24.8 / 31.9, gate|up 45.1 / 55.2, 4096 x
+// 11008 24.4 / 45.3; at 160 rows 21.8 / 27.1, 38.3 / 34.6, 63.7 / 65.5, 45.5 /
+// 44.8: they meet a little above the line.
 constexpr int64_t kI8PrefillMinM = 128;
 // Products through a decoded copy in scratch memory of frag_linear_bytes
 // (matrices of one kind, 16-bit or int8; gated: the gate and the up matrix; 0:
