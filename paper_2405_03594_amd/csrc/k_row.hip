@@ -288,19 +288,27 @@ hipError_t row_launch(const RowGroupArg& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Waves per workgroup.  Measured (us at 16 / 8 / 4 waves, bf16 at 70%): up to
+// Waves per workgroup.  A CU holds one workgroup of 16 waves, three of 8 or six
+// of 4 (80 registers).  Measured (us at 16 / 8 / 4 waves, bf16 at 70%): up to
 // one row block per CU 16 (4096 x 4096 6.3 / 7.2 / 9.1, 4096 x 11008 11.5 /
-// 14.9 / 19.2); below 3.5 8 (5120 x 5120, 1.25 per CU, of which only one fits
-// beside its 16 waves: 13.1 / 10.7 / 11.7; q|k|v, 3 per CU, 15.4 / 12.9 / 13.2);
-// above, 4 (3 x 5120 x 5120, 3.75 per CU, 23.6 / 18.2 / 17.4, at 50% 26.2 / 24.2 /
-// 22.8; 2 x 8192 x 3072, 4 per CU, 17.2 / 13.3 / 12.5; gate|up 26.6 / 19.5 / 18.8;
-// 2 x 13824 x 5120 38.7 / 27.6 / 28.3), except the gated pair, whose waves split
-// twice the matrices (21.3 / 18.0 / 20.2).
+// 14.9 / 19.2); up to three 8 (5120 x 5120, 1.25 per CU, 13.1 / 10.7 / 11.7;
+// q|k|v, three, 15.4 / 12.9 / 13.2); past them, where 8 waves would take a
+// second round, 4 (2 x 6208 x 4096, 3.03 per CU, 8 / 4 waves 14.2 / 13.8, at
+// 50% 18.2 / 17.4; 3 x 5120 x 5120 18.2 / 17.4, 24.2 / 22.8; gate|up, 5.4, 19.5 /
+// 18.8; 2 x 12288 x 4096, six, 20.0 / 19.2, 28.3 / 25.3), but 8 where those are
+// three rounds and 4 waves two of six, if the rounds are long (2 x 13824 x
+// 5120, 6.75 per CU, 27.2 / 28.2, 37.2 / 39.6; with 4096 columns 22.4 / 23.3,
+// 31.2 / 32.8; with 2048 13.9 / 14.1, and at eight per CU 15.8 / 15.4; nine per
+// CU with 4096 27.1 / 27.6, 38.3 / 38.1).  The gated pair, whose waves split
+// twice the matrices, keeps 8 (21.3 / 18.0 / 20.2).
 template <class T, bool kGated>
 hipError_t row_pick(const RowGroupArg& g, hipStream_t s) {
   const int64_t blocks = g.first[g.count], cus = device_cus();
   if (blocks <= cus) return row_launch<T, 16, kGated>(g, s);
-  return 2 * blocks < 7 * cus || kGated ? row_launch<T, 8, kGated>(g, s) : row_launch<T, 4, kGated>(g, s);
+  int64_t kmax = 0;
+  for (int i = 0; i < g.count; ++i) kmax = g.t[i].K > kmax ? g.t[i].K : kmax;
+  const bool third = blocks > 6 * cus && blocks < 9 * cus && kmax >= 4096;
+  return blocks <= 3 * cus || third || kGated ? row_launch<T, 8, kGated>(g, s) : row_launch<T, 4, kGated>(g, s);
 }
 
 // A row's activations, and a row block's words, are addressed with 32-bit byte offsets.

@@ -1,10 +1,10 @@
 """The one-row kernel (k_row.hip: AUTO at M = 1, linear groups and the gated
 half) on the GPU vs the oracle, within the parity tolerance.
 
-The shapes put its edges in play: grids of up to one, of one to 3.5 and of
-3.5 and more row blocks per CU (16, 8 or 4 waves), a last quad of one to three
-tiles, columns past K, ranges longer than one offsets window, an all-pruned
-matrix, densities on both sides of the two-quad chunk (50%), full quads off a
+The shapes put its edges in play: grids of up to one, of one to three and of
+more row blocks per CU (16, 8 or 4 waves; 8 from six to nine with 4096 columns
+and more), a last quad of one to three tiles, columns past K, ranges longer than
+one offsets window, an all-pruned matrix, densities on both sides of the two-quad chunk (50%), full quads off a
 16-byte boundary (257 value pieces), and nearly full tiles, whose upper windows
 end in the next row's or the next column group's first dword."""
 import pytest
@@ -27,7 +27,7 @@ def spl():
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("N,K,s", [(1, 8, 0.5), (33, 96, 0.7), (100, 1000, 0.5), (48, 1160, -1.0), (17, 264, 1.0),
                                    (40, 2088, 0.45), (64, 4096, 0.02), (33, 40008, 0.7), (16, 70000, 0.1),
-                                   (4128, 520, 0.7), (8200, 72, 0.0), (14330, 136, 0.6), (16390, 136, 0.6), (16390, 2056, 0.7)])
+                                   (4128, 520, 0.7), (8200, 72, 0.0), (12300, 136, 0.6), (24580, 136, 0.6), (24580, 4104, 0.9), (16390, 136, 0.6), (16390, 2056, 0.7)])
 def test_row_linear(orc, spl, dtype, N, K, s):
     W, mask = _weight(70 + N + K, N, K, dtype, s)
     X = synth.activations(71 + K, 1, K, dtype)
