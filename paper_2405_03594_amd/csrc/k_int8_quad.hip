@@ -260,14 +260,15 @@ hipError_t launch_int8_quad(const spl_int8_task* tasks, int count, int64_t M, hi
     i8q_add(g, tasks[i].Xq, tasks[i].x_scales, *tasks[i].Wq, tasks[i].w_scales, tasks[i].Y, tasks[i].acc_out);
   // Waves per row block, us per launch at 70%, 8 rows.  Up to one block per CU, where each wave has a quad, 16: 4096 x
   // 4096 6.0, with 8 6.8; 4096 x 11008 9.8, 12.4; but 2 x 2048 x 768 (6 quads) 4.5, 4.2.  Above, 16 waves are one
-  // workgroup per CU, so two rounds below two blocks per CU: 3 x 1536 x 1536 (288 blocks) 7.4, with 8 5.8.  From 3.5
-  // per CU 4, whose longer ranges hide more of a wave's start: gate|up (5.4) 15.1, with 8 19.4; 3 x 5120 x 5120 (3.75)
-  // at 1 and 12 rows 14.4, 15.0, with 8 15.6, 17.7; q|k|v (3) 11.5, 9.9.
+  // workgroup per CU, so two rounds below two blocks per CU: 3 x 1536 x 1536 (288 blocks) 7.4, with 8 5.8.  Past
+  // three per CU, which are all that it holds of 8 waves, 4, six of which fit: 2 x 6208 x 4096 (3.03) at 1 and 16 rows
+  // 11.6, 13.5, with 8 12.6, 15.4; gate|up (5.4) 15.1, 19.4; 2 x 13824 x 5120 (6.75) at one row 23.4, 24.4; q|k|v
+  // (3) 11.5, 9.9.
   int64_t kmax = 0;
   for (int i = 0; i < count; ++i) kmax = tasks[i].Wq->cols > kmax ? tasks[i].Wq->cols : kmax;
   const int64_t blocks = g.first[g.count], cus = device_cus();
   if (blocks <= cus && kmax >= 16 * 128) return i8q_launch<16>(g, s);
-  return 2 * blocks < 7 * cus ? i8q_launch<8>(g, s) : i8q_launch<4>(g, s);
+  return blocks <= 3 * cus ? i8q_launch<8>(g, s) : i8q_launch<4>(g, s);
 }
 
 }  // namespace spl
