@@ -172,10 +172,10 @@ def _stream(stream) -> ctypes.c_void_p:
     return ctypes.c_void_p(s.cuda_stream)
 
 
-def _lends(M: int, n: int, k: int, above: int) -> bool:
-    """Whether a call is offered scratch memory (the library says how much it can use): batches of more than `above`
-    rows, but for a matrix so small that it is always expanded in place."""
-    return M > above and (k > 1024 or M * n > 1 << 20)
+def _lends(M: int, n: int, k: int) -> bool:
+    """Whether a call of more rows than the streaming kernels take is offered scratch memory (the library says how
+    much it can use): not for a matrix so small that it is always expanded in place."""
+    return k > 1024 or M * n > 1 << 20
 
 
 def _scratch(need: int, device, stream) -> torch.Tensor | None:
@@ -373,7 +373,7 @@ def sparse_linear(X: torch.Tensor, Wc: SparseMatrix, out: torch.Tensor | None = 
     _arg(out, "out", shape=(M, Wc.rows), dtype=Wc.dtype)
     _dev_tensor(X, "X")
     view = Wc.view()
-    if algo == "auto" and _lends(M, Wc.rows, Wc.cols, 128):
+    if algo == "auto" and M > 128 and _lends(M, Wc.rows, Wc.cols):
         _linear_group(L, (_SparseTask * 1)(_SparseTask(X.data_ptr(), ctypes.pointer(view), out.data_ptr())), 1, M,
                       X.device, stream)
         return out
@@ -429,7 +429,7 @@ def sparse_linear_silu_mul(X: torch.Tensor, Wgate: SparseMatrix, Wup: SparseMatr
     _arg(out, "out", shape=(M, Wgate.rows), dtype=Wgate.dtype)
     _dev_tensor(X, "X")
     vg, vu = Wgate.view(), Wup.view()
-    if algo == "auto" and _lends(M, 2 * Wgate.rows, Wgate.cols, 112):
+    if algo == "auto" and M > 112 and _lends(M, 2 * Wgate.rows, Wgate.cols):
         ws = _scratch(L.spl_sparse_linear_silu_mul_scratch_bytes(M, ctypes.byref(vg), ctypes.byref(vu)), X.device,
                       stream)
         _check("spl_sparse_linear_silu_mul_scratch",
@@ -709,7 +709,7 @@ def sparse_linear_int8(Xq: torch.Tensor, x_scales: torch.Tensor, Wqc: SparseMatr
     _q_outs(out, acc_out, M, Wqc.rows)
     _q_args(Xq, x_scales, Wqc.rows, Wqc.cols, w_scales, M)
     view = Wqc.view()
-    if _lends(M, Wqc.rows, Wqc.cols, 127):
+    if M > 127 and _lends(M, Wqc.rows, Wqc.cols):
         task = _Int8Task(Xq.data_ptr(), x_scales.data_ptr(), ctypes.pointer(view), w_scales.data_ptr(),
                          out.data_ptr(), None if acc_out is None else acc_out.data_ptr())
         _int8_group(L, (_Int8Task * 1)(task), 1, M, Xq.device, stream)
